@@ -22,9 +22,10 @@
 // land in accumulators whose lanes each hold one query, and dS^T, converted
 // to bf16 in place, is the B operand of dQ^T += K^T dS^T with K^T from the
 // transposing read of the same K tile, in the matching key order.  The dkdv
-// kernel computes both key gradients from one pass over the queries with 16
-// own keys per wave and 16 x 16 x 32 products (both accumulators then fit a
-// wave's registers at two waves per SIMD); its description is at the kernel.
+// kernel is its mirror image: 32 own keys per wave, Q and dO streamed, both
+// key gradients from one pass over the queries.  Workgroups are ordered so
+// that every XCD gets its share of every batch (balanced_tile): with batch
+// after batch, the XCDs of the longer batches finished last.
 #include <type_traits>
 
 #include <mutex>
@@ -82,13 +83,6 @@ __device__ __forceinline__ i16x4 lds_read_tr16(const uint16_t* p) {
 __device__ __forceinline__ float half_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Workgroups are dispatched round-robin over the 8 XCDs: give each XCD a
-// contiguous range of logical tiles (own-row tiles of one (b, h) together).
-__device__ __forceinline__ int logical_tile(int i, int n) {
-  const int per = n >> 3, rem = n & 7, xcd = i & 7, kk = i >> 3;
-  return xcd < rem ? xcd * (per + 1) + kk : rem * (per + 1) + (xcd - rem) * per + kk;
 }
 
 // Lv of batch b (uniform).
@@ -169,6 +163,25 @@ constexpr int kDqShortTiles = 16;
 // swz(row) (each row read whole, 256 contiguous bytes).
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 1) ^ ((r & 4) ? 9 : 0) ^ (r & 8); }
 
+// Per-lane LDS element offsets of the operands in a swizzled tile:
+//   row operand, tile row l32 (+ 32 blk), d = 16 st + 8 hi: chunk 2 st + hi at
+//     2 (st ^ (swz >> 1)) + (hi ^ (swz & 1));
+//   transposed operand (transposing reads h = 0, 1 of a 16-row step), row 8 h +
+//     4 hi + (w >> 2), d = 32 mb + 16 (g & 1) + 4 (w & 3) for lane l = 16 g + w.
+__device__ __forceinline__ void row_offsets(int l32, int hi, int lane, int rk[8], int tk[2][4]) {
+  const int fr = swz(l32);
+#pragma unroll
+  for (int st = 0; st < 8; ++st) rk[st] = l32 * D + 8 * (hi ^ (fr & 1)) + 16 * (st ^ (fr >> 1));
+  const int g = lane >> 4, w = lane & 15, cc = w & 3;
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    const int row = 8 * hh + 4 * hi + (w >> 2), ft = swz(row);
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+      tk[hh][mb] = row * D + 32 * (mb ^ (ft >> 2)) + 8 * ((2 * (g & 1) + (cc >> 1)) ^ (ft & 3)) + 4 * (cc & 1);
+  }
+}
+
 template <int NWQ>
 __device__ __forceinline__ void dq_body(const BwdArgs& a) {
   constexpr int BWQ = NWQ * 32;       // queries per workgroup
@@ -176,7 +189,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
   __shared__ __attribute__((aligned(16))) uint16_t K0[STILE], K1[STILE], V0[STILE], V1[STILE];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lid = logical_tile(blockIdx.x, a.nwg);
+  const int lid = balanced_tile(blockIdx.x, a.nwg, a.B);
   const int qt = lid % a.ntile, bh = lid / a.ntile, h = bh % a.H, b = bh / a.H;
   const int tok = a.H * D, rbytes = tok * 2;
   const int lv = valid_keys(a, b);
@@ -237,26 +250,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr)(vb + (NCOPY * wave + u) * 512), 16, cg[u], 0, 0, 0);
     }
   };
-  // per-lane LDS element offsets:
-  //   key-row operand, key row l32 (+ 32 blk), d = 16 st + 8 hi: chunk 2 st +
-  //     hi at 2 (st ^ (swz >> 1)) + (hi ^ (swz & 1));
-  //   K^T operand (transposing reads h = 0, 1 of 16-key step ks), key row
-  //     16 ks + 8 h + 4 hi + (w >> 2), d = 32 mb + 16 (g & 1) + 4 (w & 3) for
-  //     lane l = 16 g + w.
   int rk[8], tk[2][4];
-  {
-    const int fr = swz(l32);
-#pragma unroll
-    for (int st = 0; st < 8; ++st) rk[st] = l32 * D + 8 * (hi ^ (fr & 1)) + 16 * (st ^ (fr >> 1));
-    const int g = lane >> 4, w = lane & 15, cc = w & 3;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int row = 8 * hh + 4 * hi + (w >> 2), ft = swz(row);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        tk[hh][mb] = row * D + 32 * (mb ^ (ft >> 2)) + 8 * ((2 * (g & 1) + (cc >> 1)) ^ (ft & 3)) + 4 * (cc & 1);
-    }
-  }
+  row_offsets(l32, hi, lane, rk, tk);
   copies(0, K0, V0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -317,86 +312,105 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
 __global__ __launch_bounds__(256, 2) void bwd_dq4_kernel(BwdArgs a) { dq_body<4>(a); }
 __global__ __launch_bounds__(512) void bwd_dq8_kernel(BwdArgs a) { dq_body<8>(a); }
 
-// ---- dK and dV together: one tile of 128 keys of one (b, h) per workgroup,
-// 16 keys per wave, with v_mfma_f32_16x16x32_bf16 (A: lane l holds row l % 16,
-// k = 8 (l / 16) .. + 7; B: column l % 16, the same k; C: column l % 16, rows
-// 4 (l / 16) .. + 3).  Per 64-query tile and query block r (16 queries):
-//   S[r] = Q K^T, dP[r] = dO V^T  (A: Q / dO rows from the padded row tile,
-//     one 16-byte read; B: the wave's own k / v rows in registers)
-//   P = exp2(S c - lse log2 e), dS = P (dP - D)   (lane: key column, 4 queries)
-//   dV^T += dO^T P, dK^T += Q^T dS over k-steps of 32 queries  (A: the
-//     transposing read of the same padded row tile, 4 queries x 16 d per
-//     16-lane group; B: P / dS, whose k order -- queries 32 s + 4 g .. + 3,
-//     then 32 s + 16 + 4 g .. + 3 for lane group g -- the two reads match).
-// Both accumulators (64 registers) and k, v (32) fit in a wave's 256
-// registers at two waves per SIMD; each query tile is copied once per
-// tensor.
-// Tiles of 64 query rows in the swizzled row layout of the dq kernel.
-constexpr int BK = 128;  // keys per workgroup
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
+// ---- dK and dV together: one tile of 256 keys of one (b, h) per workgroup,
+// 32 keys per wave, one workgroup per CU.  The mirror image of the dq kernel:
+// the own rows are keys, the streamed tiles Q and dO.  Per 64-query tile and
+// 32-query block:
+//   S = Q K^T, dP - D = dO V^T - D  (A: Q / dO rows, one 16-byte read; the
+//     dP accumulators start at -D, so the subtraction costs no vector work)
+//   P = exp2(S c - lse log2 e), dS = P (dP - D)   (lane: key column, 16 queries)
+//   dV^T += dO^T P, dK^T += Q^T dS  (A: the transposing read of the same
+//     tiles, B: P / dS from the accumulator, in the same query order)
+// Bound: LDS reads against the matrix cores.  With 32 keys a wave, each 8 KB
+// of streamed operands feed a 32 x 32 x 128 product (with 16 keys a wave half
+// of that, which held the kernel at 40 % of peak).  The two accumulators take
+// 128 registers and v 32; k does not fit beside them without spills, so each
+// wave keeps it in LDS in operand order (8 KB, one conflict-free 1 KB read
+// per product).  A key column past the valid length needs no mask: nothing of
+// it reaches another column, and the column is written as zero.
+// A workgroup with at most 128 valid keys gives each of its 32-key groups to
+// two waves, which take alternate query blocks and add up at the end (short
+// texts would leave more than half of the waves idle).
+constexpr int BK = kBwdKeys;  // keys per workgroup
+constexpr int KOWN = 32 * D;  // elements of one wave's own keys in LDS
 
 __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t Qk0[STILE], Qk1[STILE], Ok0[STILE], Ok1[STILE];
+  // the tiles' larger alignment puts them below 64 KB of LDS, where one
+  // address register a lane reaches all four through the reads' 16-bit offset
+  __shared__ __attribute__((aligned(1024))) uint16_t Qk0[STILE], Qk1[STILE], Ok0[STILE], Ok1[STILE];
+  __shared__ __attribute__((aligned(16))) uint16_t KB[NW * KOWN];
   __shared__ __attribute__((aligned(16))) float Lt[2][BN], Dt[2][BN];
-  const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lid = logical_tile(blockIdx.x, a.nwg);
+  const int lid = balanced_tile(blockIdx.x, a.nwg, a.B);
   const int kt = lid % a.ntile, sbh = lid / a.ntile, sp = sbh % a.qsplit, bh = sbh / a.qsplit;
   const int h = bh % a.H, b = bh / a.H;
   const int tok = a.H * D, rbytes = tok * 2;
   const int lv = valid_keys(a, b);
-  const int krow = kt * BK + wave * 16 + c16;
-  const bool klive = krow < a.Lk;
-  const bool kvalid = krow < lv;
-  const bool wlive = kt * BK + wave * 16 < lv;  // uniform
-  const size_t rowoff = ((size_t)b * a.Lk + (klive ? krow : 0)) * tok + (size_t)h * D;
-  f32x4 dk[8], dv[8];
+  const int nvalid = lv - kt * BK;  // valid keys of this workgroup (may be past BK, or negative)
+  const int t0 = sp * a.qper;
+  const int t1 = min(t0 + a.qper, (a.Lq + BN - 1) / BN);
+  f32x16 dk[4], dv[4];
 #pragma unroll
-  for (int mb = 0; mb < 8; ++mb) dk[mb] = dv[mb] = f32x4{};
-  // own row: lane holds key krow, d = 16 mb + 4 g .. + 3 of block mb
-  auto finish = [&](float mulk) __attribute__((always_inline)) {
-    if (!klive) return;
+  for (int mb = 0; mb < 4; ++mb) dk[mb] = dv[mb] = f32x16{};
+  // key row `row` (lane holds it), d = 32 mb + 8 g + 4 hi .. + 3: the
+  // accumulators where `row` is a valid key, zero otherwise
+  auto finish = [&](int row) __attribute__((always_inline)) {
+    if (row >= a.Lk) return;
+    const float keep = row < lv ? 1.f : 0.f;
+    const size_t rowoff = ((size_t)b * a.Lk + row) * tok + (size_t)h * D;
     if (a.qsplit > 1) {
       const size_t n = (size_t)a.B * a.Lk * tok;
       float* pk = a.part + (size_t)sp * n + rowoff;
       float* pv = a.part + (size_t)(a.qsplit + sp) * n + rowoff;
 #pragma unroll
-      for (int mb = 0; mb < 8; ++mb) {
-        *reinterpret_cast<float4*>(pk + 16 * mb + 4 * g) = make_float4(dk[mb][0], dk[mb][1], dk[mb][2], dk[mb][3]);
-        *reinterpret_cast<float4*>(pv + 16 * mb + 4 * g) = make_float4(dv[mb][0], dv[mb][1], dv[mb][2], dv[mb][3]);
-      }
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+          if (keep != 0.f) {
+            x = make_float4(dk[mb][4 * g], dk[mb][4 * g + 1], dk[mb][4 * g + 2], dk[mb][4 * g + 3]);
+            y = make_float4(dv[mb][4 * g], dv[mb][4 * g + 1], dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
+          }
+          *reinterpret_cast<float4*>(pk + 32 * mb + 8 * g + 4 * hi) = x;
+          *reinterpret_cast<float4*>(pv + 32 * mb + 8 * g + 4 * hi) = y;
+        }
     } else {
 #pragma unroll
-      for (int mb = 0; mb < 8; ++mb) {
-        uint2 x, y;
-        x.x = pack_bf16x2(dk[mb][0] * mulk, dk[mb][1] * mulk);
-        x.y = pack_bf16x2(dk[mb][2] * mulk, dk[mb][3] * mulk);
-        y.x = pack_bf16x2(dv[mb][0], dv[mb][1]);
-        y.y = pack_bf16x2(dv[mb][2], dv[mb][3]);
-        *reinterpret_cast<uint2*>(a.dk + rowoff + 16 * mb + 4 * g) = x;
-        *reinterpret_cast<uint2*>(a.dv + rowoff + 16 * mb + 4 * g) = y;
-      }
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          uint2 x = make_uint2(0u, 0u), y = x;
+          if (keep != 0.f) {
+            x.x = pack_bf16x2(dk[mb][4 * g] * a.scale, dk[mb][4 * g + 1] * a.scale);
+            x.y = pack_bf16x2(dk[mb][4 * g + 2] * a.scale, dk[mb][4 * g + 3] * a.scale);
+            y.x = pack_bf16x2(dv[mb][4 * g], dv[mb][4 * g + 1]);
+            y.y = pack_bf16x2(dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
+          }
+          *reinterpret_cast<uint2*>(a.dk + rowoff + 32 * mb + 8 * g + 4 * hi) = x;
+          *reinterpret_cast<uint2*>(a.dv + rowoff + 32 * mb + 8 * g + 4 * hi) = y;
+        }
     }
   };
-  if (kt * BK >= lv) {  // no valid key in this workgroup: zero gradient
-    finish(0.f);
+  if (nvalid <= 0 || t0 >= t1) {  // no valid key (zero gradient) or no query in this run
+    finish(kt * BK + wave * 32 + l32);
     return;
   }
-  // own k, v as B operands: lane holds key krow, d = 32 st + 8 g .. + 7
-  bf16x8 kop[4], vop[4];
+  const bool paired = nvalid <= BK / 2;  // uniform: two waves per 32-key group
+  const int kg = paired ? wave & 3 : wave, part = wave >> 2;
+  const int krow = kt * BK + kg * 32 + l32;
+  const bool wlive = kg * 32 < nvalid;  // uniform
+  const bool klive = krow < a.Lk;
+  // own k and v as B operands: lane holds key krow, chunk 2 st + hi; k goes to LDS
+  uint16_t* const kb = KB + wave * KOWN + lane * 8;
+  bf16x8 vop[8];
+  {
+    const size_t rowoff = ((size_t)b * a.Lk + (klive ? krow : 0)) * tok + (size_t)h * D;
+    bf16x8 kop[8];
+    own_operand(a.k + rowoff, klive, hi, kop);
+    own_operand(a.v + rowoff, klive, hi, vop);
 #pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    uint4 x = make_uint4(0, 0, 0, 0), y = x;
-    if (klive) {
-      x = *reinterpret_cast<const uint4*>(a.k + rowoff + 32 * st + 8 * g);
-      y = *reinterpret_cast<const uint4*>(a.v + rowoff + 32 * st + 8 * g);
-    }
-    kop[st] = __builtin_bit_cast(bf16x8, x);
-    vop[st] = __builtin_bit_cast(bf16x8, y);
+    for (int st = 0; st < 8; ++st) *reinterpret_cast<bf16x8*>(kb + st * 512) = kop[st];
   }
 
   const uint16_t* qbh = a.q + (size_t)b * a.Lq * tok + (size_t)h * D;
@@ -408,55 +422,38 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int row = 4 * (2 * wave + u) + (lane >> 4);
-    cg[u] = row * rbytes + (c16 ^ swz(row)) * 16;
+    cg[u] = row * rbytes + ((lane & 15) ^ swz(row)) * 16;
   }
   auto copy_tile = [&](__amdgpu_buffer_rsrc_t rs, uint16_t* buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 2; ++u)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + (2 * wave + u) * 512), 16, cg[u], 0, 0, 0);
   };
-  const int t0 = sp * a.qper;
-  const int t1 = min(t0 + a.qper, (a.Lq + BN - 1) / BN);
   float lrow = INFINITY, drow = 0.f;
   auto copies = [&](int t, uint16_t* qk, uint16_t* ok) __attribute__((always_inline)) {
     copy_tile(tile_rsrc(qbh, t, a.Lq, tok), qk);
     copy_tile(tile_rsrc(obh, t, a.Lq, tok), ok);
     if (tid < BN) {
       const int r = t * BN + tid;
-      lrow = r < a.Lq ? lseb[r] : INFINITY;
+      lrow = r < a.Lq ? lseb[r] : INFINITY;  // rows past Lq: P = 0
       drow = r < a.Lq ? delb[r] : 0.f;
     }
   };
   auto put_rows = [&](int buf) __attribute__((always_inline)) {
     if (tid < BN) {
-      Lt[buf][tid] = lrow * kLog2e;
-      Dt[buf][tid] = drow;
+      Lt[buf][tid] = -lrow * kLog2e;
+      Dt[buf][tid] = -drow;
     }
   };
-  if (t0 >= t1) {
-    finish(0.f);
-    return;
-  }
   copies(t0, Qk0, Ok0);
   put_rows(0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  // per-lane LDS element offsets (rows of a 16-row block share swz):
-  //   row operand, query row 16 r + c16, d = 32 st + 8 g: chunk 4 st + g,
-  //     placed at 4 (st ^ (swz >> 2)) + ((g ^ swz) & 3);
-  //   transposing read, query row 4 g + (c16 >> 2) of a 16-row block, d =
-  //     16 mb + 4 (c16 & 3): 8 bytes of chunk pair mb, placed at pair
-  //     mb ^ (swz >> 1), chunk ((c16 >> 1) & 1) ^ (swz & 1) of the pair.
-  int roff[4], toff[8];
-  {
-    const int fr = swz(c16);
-#pragma unroll
-    for (int st = 0; st < 4; ++st) roff[st] = c16 * D + 8 * (4 * (st ^ (fr >> 2)) + ((g ^ fr) & 3));
-    const int tr = 4 * g + (c16 >> 2), ft = swz(tr), cc = c16 & 3;
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) toff[mb] = tr * D + 16 * (mb ^ (ft >> 1)) + 8 * ((cc >> 1) ^ (ft & 1)) + 4 * (cc & 1);
-  }
+  // per-lane LDS element offsets of the row operand and of the transposing
+  // reads, as in the dq kernel (tile rows are queries here)
+  int rk[8], tk[2][4];
+  row_offsets(l32, hi, lane, rk, tk);
   auto step = [&](auto par, int t) __attribute__((always_inline)) {
     constexpr int P = decltype(par)::value;
     const uint16_t* qt = P ? Qk1 : Qk0;
@@ -464,49 +461,47 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
     if (t + 1 < t1) copies(t + 1, P ? Qk0 : Qk1, P ? Ok0 : Ok1);
     if (wlive) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        f32x4 sc[2], dp[2];
+      for (int blk = 0; blk < 2; ++blk) {
+        if (paired && blk != part) continue;  // uniform
+        f32x16 s = f32x16{}, dp;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int r = 2 * s + u;
-          sc[u] = dp[u] = f32x4{};
-#pragma unroll
-          for (int st = 0; st < 4; ++st) {
-            const bf16x8 qa = *reinterpret_cast<const bf16x8*>(qt + 16 * r * D + roff[st]);
-            const bf16x8 oa = *reinterpret_cast<const bf16x8*>(ot + 16 * r * D + roff[st]);
-            sc[u] = mfma16(qa, kop[st], sc[u]);
-            dp[u] = mfma16(oa, vop[st], dp[u]);
-          }
+        for (int g = 0; g < 4; ++g) {
+          const float4 d4 = *reinterpret_cast<const float4*>(&Dt[P][32 * blk + 8 * g + 4 * hi]);
+          dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
         }
-        // P and dS of queries 16 r + 4 g + i (i = 0..3), r = 2 s + u
-        uint32_t pw[4], dw[4];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int r0 = 16 * (2 * s + u) + 4 * g;
-          const float4 l4 = *reinterpret_cast<const float4*>(&Lt[P][r0]);
-          const float4 d4 = *reinterpret_cast<const float4*>(&Dt[P][r0]);
-          const float lr[4] = {l4.x, l4.y, l4.z, l4.w}, dr[4] = {d4.x, d4.y, d4.z, d4.w};
-          float pp[4], dd[4];
+        for (int st = 0; st < 8; ++st) {
+          s = mfma32(*reinterpret_cast<const bf16x8*>(qt + 32 * blk * D + rk[st]),
+                     *reinterpret_cast<const bf16x8*>(kb + st * 512), s);
+          dp = mfma32(*reinterpret_cast<const bf16x8*>(ot + 32 * blk * D + rk[st]), vop[st], dp);
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 l4 = *reinterpret_cast<const float4*>(&Lt[P][32 * blk + 8 * g + 4 * hi]);
+          const float nl[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            pp[i] = kvalid ? __builtin_amdgcn_exp2f(fmaf(sc[u][i], a.c, -lr[i])) : 0.f;
-            dd[i] = pp[i] * (dp[u][i] - dr[i]);
+            s[4 * g + i] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + i], a.c, nl[i]));
+            dp[4 * g + i] *= s[4 * g + i];
           }
-          pw[2 * u] = pack_bf16x2(pp[0], pp[1]);
-          pw[2 * u + 1] = pack_bf16x2(pp[2], pp[3]);
-          dw[2 * u] = pack_bf16x2(dd[0], dd[1]);
-          dw[2 * u + 1] = pack_bf16x2(dd[2], dd[3]);
         }
-        const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
-        const bf16x8 db = __builtin_bit_cast(bf16x8, make_uint4(dw[0], dw[1], dw[2], dw[3]));
-        // dV^T += dO^T P, dK^T += Q^T dS over queries 32 s .. 32 s + 31
+        bf16x8 pb[2], db[2];
+        pack_ops(s, pb);
+        pack_ops(dp, db);
+        // dV^T += dO^T P, dK^T += Q^T dS over the block's 32 queries
 #pragma unroll
-        for (int mb = 0; mb < 8; ++mb) {
-          const int o0 = 32 * s * D + toff[mb];
-          const i16x4 olo = lds_read_tr16(ot + o0), ohi = lds_read_tr16(ot + o0 + 16 * D);
-          const i16x4 qlo = lds_read_tr16(qt + o0), qhi = lds_read_tr16(qt + o0 + 16 * D);
-          dv[mb] = mfma16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(olo, ohi, 0, 1, 2, 3, 4, 5, 6, 7)), pb, dv[mb]);
-          dk[mb] = mfma16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(qlo, qhi, 0, 1, 2, 3, 4, 5, 6, 7)), db, dk[mb]);
+        for (int k2 = 0; k2 < 2; ++k2) {
+          const int o0 = 16 * (2 * blk + k2) * D;
+#pragma unroll
+          for (int mb = 0; mb < 4; ++mb) {
+            const i16x4 olo = lds_read_tr16(ot + o0 + tk[0][mb]), ohi = lds_read_tr16(ot + o0 + tk[1][mb]);
+            dv[mb] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(olo, ohi, 0, 1, 2, 3, 4, 5, 6, 7)), pb[k2], dv[mb]);
+          }
+#pragma unroll
+          for (int mb = 0; mb < 4; ++mb) {
+            const i16x4 qlo = lds_read_tr16(qt + o0 + tk[0][mb]), qhi = lds_read_tr16(qt + o0 + tk[1][mb]);
+            dk[mb] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(qlo, qhi, 0, 1, 2, 3, 4, 5, 6, 7)), db[k2], dk[mb]);
+          }
         }
       }
     }
@@ -522,7 +517,38 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
     step(odd(), t + 1);
   }
   if (t < t1) step(even(), t);
-  finish(a.scale);
+  if (paired) {
+    // waves 4..7 hand their sums to waves 0..3 through the buffers (all free
+    // after the last step's barrier): dK in the own-key area, dV in the tiles
+    float* const xk = reinterpret_cast<float*>(KB) + kg * 4096 + lane * 4;
+    float* const xv = reinterpret_cast<float*>(kg == 0 ? Qk0 : kg == 1 ? Qk1 : kg == 2 ? Ok0 : Ok1) + lane * 4;
+    if (part == 1) {
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          *reinterpret_cast<float4*>(xk + (4 * mb + g) * 256) =
+              make_float4(dk[mb][4 * g], dk[mb][4 * g + 1], dk[mb][4 * g + 2], dk[mb][4 * g + 3]);
+          *reinterpret_cast<float4*>(xv + (4 * mb + g) * 256) =
+              make_float4(dv[mb][4 * g], dv[mb][4 * g + 1], dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
+        }
+    }
+    __syncthreads();
+    if (part == 1) {
+      finish(krow + BK / 2);  // the upper half of the tile holds no valid key: zero
+      return;
+    }
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 x = *reinterpret_cast<const float4*>(xk + (4 * mb + g) * 256);
+        const float4 y = *reinterpret_cast<const float4*>(xv + (4 * mb + g) * 256);
+        dk[mb][4 * g] += x.x; dk[mb][4 * g + 1] += x.y; dk[mb][4 * g + 2] += x.z; dk[mb][4 * g + 3] += x.w;
+        dv[mb][4 * g] += y.x; dv[mb][4 * g + 1] += y.y; dv[mb][4 * g + 2] += y.z; dv[mb][4 * g + 3] += y.w;
+      }
+  }
+  finish(krow);
 }
 
 // ---- dK = scale * sum of the partials, dV = sum of the partials (qsplit >

@@ -646,28 +646,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(AttnArgs a) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lse), rl, olive && hi == 0 ? orow * 4 : 0x7ffffff0, 0, 0);
   };
 
-  // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
-  // contiguous range of positions so the query tiles of one (b, h) share
-  // that XCD's L2 for the K/V stream.  The positions run over the eighths of
-  // every batch in turn (eighth 0 of batch 0, of batch 1, ..., eighth 1 of
-  // batch 0, ...), so that each XCD gets about an eighth of every batch:
-  // batches of different valid lengths then load the XCDs evenly (with
-  // batch after batch, the XCDs holding the longer batches finished last).
-  // One batch: position = logical tile.
-  int lid;
-  {
-    const int i = blockIdx.x, n = a.nwg;
-    const int per = n >> 3, rem = n & 7, xcd = i & 7, kk = i >> 3;
-    const int pos = xcd < rem ? xcd * (per + 1) + kk : rem * (per + 1) + (xcd - rem) * per + kk;
-    const int N = a.nwg / a.B;  // tiles per batch: eighth c holds p + (c < r) of them
-    const int p = N >> 3, r = N & 7;
-    const int big = a.B * r * (p + 1);  // positions in the eighths of size p + 1
-    const int c = pos < big ? pos / (a.B * (p + 1)) : r + (pos - big) / (a.B * p);
-    const int sc = c < r ? p + 1 : p;
-    const int cs = c * p + min(c, r);  // start of eighth c within a batch
-    const int rm = pos - a.B * cs;
-    lid = (rm / sc) * N + cs + rm % sc;
-  }
+  const int lid = balanced_tile(blockIdx.x, a.nwg, a.B);  // XCD-aware
   begin_tile(lid);
   reset_acc();
   if (lv == 0) {  // no valid key: O = 0, LSE = -inf

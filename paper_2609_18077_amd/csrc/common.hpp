@@ -86,4 +86,25 @@ __host__ __device__ inline PairSlot pair_slot(const RopeParams& r, int pi) {
   return s;
 }
 
+// Logical tile of workgroup i of n (n / B per batch, batch after batch).
+// Workgroups are dispatched round-robin over the 8 XCDs; each XCD gets a
+// contiguous range of positions, so that the tiles of one (b, h) share that
+// XCD's L2.  The positions run over the eighths of every batch in turn (eighth
+// 0 of batch 0, of batch 1, ..., eighth 1 of batch 0, ...), so that each XCD
+// gets about an eighth of every batch: batches of different valid lengths then
+// load the XCDs evenly (with batch after batch, the XCDs holding the longer
+// batches finished last).  One batch: position = logical tile.
+__device__ __forceinline__ int balanced_tile(int i, int n, int B) {
+  const int per = n >> 3, rem = n & 7, xcd = i & 7, kk = i >> 3;
+  const int pos = xcd < rem ? xcd * (per + 1) + kk : rem * (per + 1) + (xcd - rem) * per + kk;
+  const int N = n / B;  // tiles per batch: eighth c holds p + (c < r) of them
+  const int p = N >> 3, r = N & 7;
+  const int big = B * r * (p + 1);  // positions in the eighths of size p + 1
+  const int c = pos < big ? pos / (B * (p + 1)) : r + (pos - big) / (B * p);
+  const int sc = c < r ? p + 1 : p;
+  const int cs = c * p + (c < r ? c : r);  // start of eighth c within a batch
+  const int rm = pos - B * cs;
+  return (rm / sc) * N + cs + rm % sc;
+}
+
 }  // namespace vidax

@@ -23,32 +23,41 @@ hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int B, int L, int H, co
 // Compute units of the current device (queried once per device).
 int device_cu_count();
 
-// Query-stream split of the backward's key-side kernel.  Its workgroups
-// own 128 keys of one (b, h) and stream every query in 64-row tiles; when
-// there are fewer of them than twice the compute units, the query tiles are
-// cut into qsplit runs of qper tiles (at least 8 tiles a run, at most 16
-// runs) so that about four workgroups per compute unit exist.  The fp32
-// partial dK and dV of the runs follow D in the workspace, from a 256-byte
-// aligned offset; `floats` is the workspace size this needs (B * H * Lq when
-// qsplit is 1).
+// Query-stream split of the backward's key-side kernel.  Its workgroups own
+// kBwdKeys keys of one (b, h), one workgroup per compute unit, and stream
+// every query in 64-row tiles; where there are fewer of them than twice the
+// compute units, the query tiles may be cut into qsplit runs of qper tiles
+// (at least 2 tiles a run, at most 32 runs).  Chosen: the least time in units
+// of one tile's (about 3.6 us): rounds x (tiles a run + 2 for a workgroup's
+// start and end), and for a split 3 for the extra launch and the bytes of the
+// fp32 partials (written and read: 16 bytes a gradient value and run, about
+// 14 MB in a tile's time).  The partial dK and dV of the runs follow D in the
+// workspace, from a 256-byte aligned offset; `floats` is the workspace size
+// this needs (B * H * Lq when qsplit is 1).
+constexpr int kBwdKeys = 256;
 struct BwdSplit {
   int qsplit, qper;
   size_t part_offset, floats;
 };
 
 inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus) {
-  constexpr int kRows = 64, kOwn = 128;
+  constexpr int kRows = 64;
   BwdSplit r;
   const size_t rows = (size_t)B * H * Lq;
   const int qtiles = (Lq + kRows - 1) / kRows;
-  const long nkv = (long)((Lk + kOwn - 1) / kOwn) * B * H;
+  const int64_t nkv = (int64_t)((Lk + kBwdKeys - 1) / kBwdKeys) * B * H;
   r.qsplit = 1;
-  if (nkv > 0 && nkv < 2L * cus) {
-    long want = (4L * cus + nkv - 1) / nkv;
-    const long cap = qtiles / 8;
-    if (want > cap) want = cap;
-    if (want > 16) want = 16;
-    if (want > 1) r.qsplit = (int)want;
+  if (nkv > 0 && nkv < 2 * (int64_t)cus) {
+    const double part = (double)B * Lk * H * kHeadDim * 16 / 14e6;
+    double best = 0;
+    for (int s = 1; s <= 32 && (s == 1 || s <= qtiles / 2); ++s) {
+      const double rounds = (double)((nkv * s + cus - 1) / cus);
+      const double cost = rounds * ((qtiles + s - 1) / s + 2) + (s > 1 ? 3 + s * part : 0);
+      if (s == 1 || cost < best) {
+        best = cost;
+        r.qsplit = s;
+      }
+    }
   }
   r.qper = (qtiles + r.qsplit - 1) / r.qsplit;
   r.part_offset = (rows + 63) / 64 * 64;

@@ -128,6 +128,18 @@ def test_attn_bwd_matches_oracle(w):
     _bwd_case(w)
 
 
+@pytest.mark.parametrize("Lq,Lk,lens", [
+    (200, 512, [1, 32, 33]),       # at most 128 valid keys: two waves a 32-key group
+    (321, 300, [127, 128, 129]),   # the edge between the two forms
+    (64, 513, [256, 257, 513]),    # one query tile; the edge of a 256-key workgroup
+    (130, 256, [97, 255, 300]),    # split into one-tile runs where it splits
+], ids=str)
+def test_attn_bwd_key_groups(Lq, Lk, lens):
+    """Valid lengths at the edges of the key-side kernel's 32-key groups, of
+    its two forms (up to and past 128 valid keys) and of its 256-key tiles."""
+    _bwd_case(inputs.custom("bwd_keys", B=3, H=2, Lq=Lq, Lk=Lk, seed=39, kv_valid=("fixed", lens)))
+
+
 def _random_bwd_shapes(n=10, seed=2027):
     """Seeded random shapes: batches, heads, query and key counts off the
     256-row and 64-row tile grids, per-batch valid lengths from 0 to past Lk
