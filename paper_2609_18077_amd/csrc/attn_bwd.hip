@@ -26,9 +26,9 @@
 // key gradients from one pass over the queries.  Workgroups are ordered so
 // that every XCD gets its share of every batch (balanced_tile): with batch
 // after batch, the XCDs of the longer batches finished last.
-#include <type_traits>
-
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "launch.hpp"
 
@@ -111,17 +111,27 @@ __device__ __forceinline__ void own_operand(const uint16_t* p, bool live, int hi
   }
 }
 
-// A 32 x 32 fp32 accumulator (tile rows x own rows) -> two bf16 B operands of
-// 16 tile rows each, in the accumulator's row order.
-[[maybe_unused]] __device__ __forceinline__ void pack_ops(const f32x16& x, bf16x8 op[2]) {
+// Rows 16 k2 .. + 15 of a 32 x 32 fp32 accumulator (tile rows x own rows) ->
+// a bf16 B operand, in the accumulator's row order.
+__device__ __forceinline__ bf16x8 pack8(const f32x16& x, int k2) {
+  uint32_t w[4];
 #pragma unroll
-  for (int k2 = 0; k2 < 2; ++k2) {
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) w[e >> 1] = pack_bf16x2(x[8 * k2 + e], x[8 * k2 + e + 1]);
-    op[k2] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-  }
+  for (int e = 0; e < 8; e += 2) w[e >> 1] = pack_bf16x2(x[8 * k2 + e], x[8 * k2 + e + 1]);
+  return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
 }
+
+// f(0), ..., f(N - 1) with compile-time arguments.
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_slots_of(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_slots(F&& f) {
+  for_slots_of<N>(f, std::make_integer_sequence<int, N>());
+}
+
+// End of a slot of a hand-scheduled block: no instruction moves across it.
+#define SLOT() __builtin_amdgcn_sched_barrier(0)
 
 // Tile row (0..63) of register i of accumulator blk for lane half hi.
 [[maybe_unused]] __device__ __forceinline__ int acc_row(int blk, int i, int hi) { return 32 * blk + 8 * (i >> 2) + 4 * hi + (i & 3); }
@@ -154,32 +164,46 @@ constexpr int STILE = BN * D;  // elements of a swizzled tile
 constexpr int kDqShortTiles = 16;
 
 // Tiles of 64 rows sit in LDS as 256-byte rows whose 16-byte chunks are
-// permuted: chunk c of row r at position c ^ swz(r), swz linear in the bits
-// of r & 15 (bit 0 -> 2, bit 1 -> 4, bit 2 -> 9, bit 3 -> 8), found by
-// exhaustive search: the rows of every operand read of the dq and dkdv
-// kernels then fall on distinct banks, whether the LDS serves 128 or 256
-// bytes a cycle.  Copy j of a tile fills rows 4 j .. 4 j + 3: lane l writes
+// permuted: chunk c of row r at position c ^ swz(r), swz(r) = 4 (r mod 4) +
+// (r / 4) mod 4.  Any 4 consecutive rows then put a 64-byte span into 4
+// different quarters of the banks (the transposing reads), and the 16 rows of
+// a row read's phase put one chunk into 16 different places: no bank
+// conflicts.  Copy j of a tile fills rows 4 j .. 4 j + 3: lane l writes
 // position l & 15 of row 4 j + (l >> 4), fetching its chunk (l & 15) ^
 // swz(row) (each row read whole, 256 contiguous bytes).
-__device__ __forceinline__ int swz(int r) { return ((r & 3) << 1) ^ ((r & 4) ? 9 : 0) ^ (r & 8); }
+__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 
-// Per-lane LDS element offsets of the operands in a swizzled tile:
-//   row operand, tile row l32 (+ 32 blk), d = 16 st + 8 hi: chunk 2 st + hi at
-//     2 (st ^ (swz >> 1)) + (hi ^ (swz & 1));
-//   transposed operand (transposing reads h = 0, 1 of a 16-row step), row 8 h +
-//     4 hi + (w >> 2), d = 32 mb + 16 (g & 1) + 4 (w & 3) for lane l = 16 g + w.
-__device__ __forceinline__ void row_offsets(int l32, int hi, int lane, int rk[8], int tk[2][4]) {
-  const int fr = swz(l32);
-#pragma unroll
-  for (int st = 0; st < 8; ++st) rk[st] = l32 * D + 8 * (hi ^ (fr & 1)) + 16 * (st ^ (fr >> 1));
-  const int g = lane >> 4, w = lane & 15, cc = w & 3;
-#pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
-    const int row = 8 * hh + 4 * hi + (w >> 2), ft = swz(row);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-      tk[hh][mb] = row * D + 32 * (mb ^ (ft >> 2)) + 8 * ((2 * (g & 1) + (cc >> 1)) ^ (ft & 3)) + 4 * (cc & 1);
-  }
+// Per-lane LDS element offsets of the operands in a swizzled tile, one register
+// each (the step's constants enter by XOR):
+//   row operand st, tile row l32 (+ 32 blk), d = 16 st + 8 hi: chunk 2 st + hi
+//     of the row at row ^ (16 st);
+//   transposed operand mb (reads h = 0, 1 of a 16-row step), row 8 h + 4 hi +
+//     (w >> 2), d = 32 mb + 16 (g & 1) + 4 (w & 3) for lane l = 16 g + w: at
+//     (tr ^ (32 mb) ^ (16 h)) + 8 h rows.
+struct TileOffsets {
+  int row, tr;
+};
+__device__ __forceinline__ TileOffsets tile_offsets(int lane) {
+  const int l32 = lane & 31, hi = lane >> 5, g = lane >> 4, w = lane & 15, r = 4 * hi + (w >> 2);
+  TileOffsets o;
+  o.row = l32 * D + 8 * (hi ^ swz(l32));
+  o.tr = r * D + 8 * ((2 * (g & 1) + ((w >> 1) & 1)) ^ swz(r)) + 4 * (w & 1);
+  return o;
+}
+// x, as a value of iteration t: what is computed from it stays in the loop
+// (hoisted, every buffer's addresses would live in registers of their own
+// instead of in the reads' immediate offsets).
+__device__ __forceinline__ int in_loop(int x, int t) {
+  asm("" : "+v"(x) : "s"(t));
+  return x;
+}
+__device__ __forceinline__ bf16x8 read_row(const uint16_t* tile, int row, int st) {
+  return *reinterpret_cast<const bf16x8*>(tile + (row ^ (16 * st)));
+}
+__device__ __forceinline__ bf16x8 read_tr(const uint16_t* rows16, int tr, int mb) {
+  const i16x4 lo = lds_read_tr16(rows16 + (tr ^ (32 * mb)));
+  const i16x4 up = lds_read_tr16(rows16 + (tr ^ (32 * mb) ^ 16) + 8 * D);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 template <int NWQ>
@@ -250,60 +274,94 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr)(vb + (NCOPY * wave + u) * 512), 16, cg[u], 0, 0, 0);
     }
   };
-  int rk[8], tk[2][4];
-  row_offsets(l32, hi, lane, rk, tk);
+  const TileOffsets off = tile_offsets(lane);
   copies(0, K0, V0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  auto step = [&](auto par, int j) __attribute__((always_inline)) {
+  // One tile, hand-scheduled: one slot per product, each slot also issuing the
+  // operand reads of the product three slots later and its share of the vector
+  // work.  S of block 0, dP of block 0 beside its exponentials, S of block 1
+  // beside dS of block 0, dP of block 1 beside its exponentials, dQ of block 0
+  // beside dS of block 1, dQ of block 1: no product waits for the vector work
+  // before it.  At 32760 x 32760 x 12 heads: matrix cores busy 64 -> 76 % of the
+  // cycles, 8.16 -> 7.60 ms (the clock falls from 1.82 to 1.63 GHz: at this load
+  // the board's power holds it).  TAIL: the last tile, whose keys past Lv get P = 0.
+  auto step = [&](auto par, auto tl, int j) __attribute__((always_inline)) {
     constexpr int P = decltype(par)::value;
+    constexpr bool TAIL = decltype(tl)::value;
     const uint16_t* kt = P ? K1 : K0;
     const uint16_t* vt = P ? V1 : V0;
-    if (j + 1 < ntiles) copies(j + 1, P ? K0 : K1, P ? V0 : V1);
-    const bool tail = j * BN + BN > lv;
-    // one 32-key block at a time: fewer live registers, and the products of
-    // the second block overlap the first block's exponentials
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-      for (int st = 0; st < 8; ++st) {
-        s = mfma32(*reinterpret_cast<const bf16x8*>(kt + 32 * blk * D + rk[st]), qop[st], s);
-        dp = mfma32(*reinterpret_cast<const bf16x8*>(vt + 32 * blk * D + rk[st]), dop[st], dp);
+    if (!TAIL) copies(j + 1, P ? K0 : K1, P ? V0 : V1);
+    const int orow = in_loop(off.row, j), otr = in_loop(off.tr, j);
+    // operand reads in the order of their products: S0, dP0, S1, dP1, dQ0, dQ1
+    bf16x8 op[48];
+    auto read_op = [&](auto N) __attribute__((always_inline)) {
+      constexpr int n = decltype(N)::value;
+      if constexpr (n < 48) {
+        constexpr int blk = n < 32 ? n >> 4 : (n - 32) >> 3;
+        if constexpr (n >= 32) op[n] = read_tr(kt + (32 * blk + 16 * ((n >> 2) & 1)) * D, otr, n & 3);
+        else op[n] = read_row((n & 8 ? vt : kt) + 32 * blk * D, orow, n & 7);
       }
+    };
+    f32x16 sc[2], dp[2];
+    bf16x8 ds[2][2];
+    const int left = lv - j * BN - 4 * hi;  // TAIL: valid keys of the tile, from this lane half's first
+    auto exps = [&](int blk, int i0) __attribute__((always_inline)) {  // P of elements i0, i0 + 1
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], a.c, -lse2)) * (dp[i] - dl);
-      if (tail) {  // uniform: only the last, ragged key tile; keys past Lv get dS = 0
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (j * BN + acc_row(blk, i, hi) >= lv) s[i] = 0.f;
+      for (int i = i0; i < i0 + 2; ++i) {
+        const float x = fmaf(sc[blk][i], a.c, -lse2);
+        sc[blk][i] = __builtin_amdgcn_exp2f(TAIL && acc_row(blk, i, 0) >= left ? -INFINITY : x);
       }
-      bf16x8 dsop[2];
-      pack_ops(s, dsop);
+    };
+    auto mul4 = [&](int blk, int i0) __attribute__((always_inline)) {  // dS of elements i0 .. i0 + 3
 #pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2) {
-        const int ks = 2 * blk + k2;
+      for (int i = i0; i < i0 + 4; ++i) dp[blk][i] *= sc[blk][i];
+    };
+    for_slots<3>(read_op);
+    SLOT();
+    for_slots<48>([&](auto N) __attribute__((always_inline)) {
+      constexpr int n = decltype(N)::value, blk = n < 32 ? n >> 4 : (n - 32) >> 3, u = n & 7;
+      if constexpr (n >= 32) acc[u & 3] = mfma32(op[n], ds[blk][u >> 2], acc[u & 3]);
+      else if constexpr (n & 8) {
+        if constexpr (u == 0)
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-          const i16x4 lo = lds_read_tr16(kt + 16 * ks * D + tk[0][mb]);
-          const i16x4 up = lds_read_tr16(kt + 16 * ks * D + tk[1][mb]);
-          acc[mb] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7)),
-                           dsop[k2], acc[mb]);
-        }
+          for (int i = 0; i < 16; ++i) dp[blk][i] = -dl;
+        dp[blk] = mfma32(op[n], dop[u], dp[blk]);
       }
+      else sc[blk] = mfma32(op[n], qop[u], u == 0 ? f32x16{} : sc[blk]);
+      read_op(std::integral_constant<int, n + 3>());
+      // vector work of block 0 from its second dP slot on (10), of block 1 from 26 on:
+      // eight slots of exponentials, four of products, the packs
+      for_slots<2>([&](auto V) __attribute__((always_inline)) {
+        constexpr int vb = decltype(V)::value, r = n - (vb ? 26 : 10);
+        if constexpr (r >= 0 && r < 8) exps(vb, 2 * r);
+        if constexpr (r >= 8 && r < 12) mul4(vb, 4 * (r - 8));
+        if constexpr (r == 10) ds[vb][0] = pack8(dp[vb], 0);
+        if constexpr (r == 12) ds[vb][1] = pack8(dp[vb], 1);
+      });
+      SLOT();
+    });
+    if (!TAIL) {
+      __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed
+      __syncthreads();
     }
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed
-    __syncthreads();
   };
   using even = std::integral_constant<int, 0>;
   using odd = std::integral_constant<int, 1>;
+  using full = std::false_type;
+  using last = std::true_type;
   int j = 0;
-  for (; j + 1 < ntiles; j += 2) {
-    step(even(), j);
-    step(odd(), j + 1);
+  for (; j + 2 < ntiles; j += 2) {
+    step(even(), full(), j);
+    step(odd(), full(), j + 1);
   }
-  if (j < ntiles) step(even(), j);
+  if (j + 1 < ntiles) {
+    step(even(), full(), j);
+    step(odd(), last(), j + 1);
+  } else {
+    step(even(), last(), j);
+  }
   if (qlive) store_own(dqp, acc, a.scale, hi);
 }
 
@@ -323,7 +381,7 @@ __global__ __launch_bounds__(512) void bwd_dq8_kernel(BwdArgs a) { dq_body<8>(a)
 //     tiles, B: P / dS from the accumulator, in the same query order)
 // Bound: LDS reads against the matrix cores.  With 32 keys a wave, each 8 KB
 // of streamed operands feed a 32 x 32 x 128 product (with 16 keys a wave half
-// of that, which held the kernel at 40 % of peak).  The two accumulators take
+// of that: 13.7 -> 11.2 ms at 32760 x 32760 x 12 heads).  The two accumulators take
 // 128 registers and v 32; k does not fit beside them without spills, so each
 // wave keeps it in LDS in operand order (8 KB, one conflict-free 1 KB read
 // per product).  A key column past the valid length needs no mask: nothing of
@@ -450,58 +508,84 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  // per-lane LDS element offsets of the row operand and of the transposing
-  // reads, as in the dq kernel (tile rows are queries here)
-  int rk[8], tk[2][4];
-  row_offsets(l32, hi, lane, rk, tk);
+  const TileOffsets off = tile_offsets(lane);
   auto step = [&](auto par, int t) __attribute__((always_inline)) {
     constexpr int P = decltype(par)::value;
     const uint16_t* qt = P ? Qk1 : Qk0;
     const uint16_t* ot = P ? Ok1 : Ok0;
     if (t + 1 < t1) copies(t + 1, P ? Qk0 : Qk1, P ? Ok0 : Ok1);
+    const int orow = in_loop(off.row, t), otr = in_loop(off.tr, t);
     if (wlive) {
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
         if (paired && blk != part) continue;  // uniform
+        // Hand-scheduled: one slot per product, each slot also issuing the
+        // operand reads of the product three slots later and its share of
+        // the vector work, so that a wave waits neither for LDS nor for its
+        // exponentials (left to the compiler, every score product waited for
+        // a read issued just before it).  At 32760 x 32760 x 12 heads: matrix
+        // cores busy 58 -> 73 % of the cycles, 11.2 -> 10.3 ms (clock 1.94 ->
+        // 1.68 GHz).
+        const uint16_t* qb = qt + 32 * blk * D;
+        const uint16_t* ob = ot + 32 * blk * D;
         f32x16 s = f32x16{}, dp;
+        bf16x8 qa[8], ka[8], oa[8], ta[8], tb[8], pb[2], db[2];
+        float4 nl[4];
+        auto exps = [&](int i) __attribute__((always_inline)) {  // P of elements i, i + 1
+          const float4 l4 = nl[i >> 2];
+          s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], a.c, (i & 2) ? l4.z : l4.x));
+          s[i + 1] = __builtin_amdgcn_exp2f(fmaf(s[i + 1], a.c, (i & 2) ? l4.w : l4.y));
+        };
+        auto read_qk = [&](int st) __attribute__((always_inline)) {
+          qa[st] = read_row(qb, orow, st);
+          ka[st] = *reinterpret_cast<const bf16x8*>(kb + st * 512);
+        };
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 d4 = *reinterpret_cast<const float4*>(&Dt[P][32 * blk + 8 * g + 4 * hi]);
-          dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
+        for (int st = 0; st < 3; ++st) read_qk(st);
+        SLOT();
+#pragma unroll
+        for (int st = 0; st < 8; ++st) {  // S
+          s = mfma32(qa[st], ka[st], s);
+          if (st + 3 < 8) read_qk(st + 3);
+          else oa[st - 5] = read_row(ob, orow, st - 5);
+          if (st >= 1 && st < 5) {
+            const float4 d4 = *reinterpret_cast<const float4*>(&Dt[P][32 * blk + 8 * (st - 1) + 4 * hi]);
+            dp[4 * st - 4] = d4.x; dp[4 * st - 3] = d4.y; dp[4 * st - 2] = d4.z; dp[4 * st - 1] = d4.w;
+          }
+          SLOT();
         }
 #pragma unroll
-        for (int st = 0; st < 8; ++st) {
-          s = mfma32(*reinterpret_cast<const bf16x8*>(qt + 32 * blk * D + rk[st]),
-                     *reinterpret_cast<const bf16x8*>(kb + st * 512), s);
-          dp = mfma32(*reinterpret_cast<const bf16x8*>(ot + 32 * blk * D + rk[st]), vop[st], dp);
+        for (int st = 0; st < 8; ++st) {  // dP - D; P of elements 0 .. 11
+          dp = mfma32(oa[st], vop[st], dp);
+          if (st + 3 < 8) oa[st + 3] = read_row(ob, orow, st + 3);
+          else ta[st - 5] = read_tr(ob, otr, st - 5);
+          if (st < 4) nl[st] = *reinterpret_cast<const float4*>(&Lt[P][32 * blk + 8 * st + 4 * hi]);
+          if (st >= 2) exps(2 * (st - 2));
+          if (st == 6) pb[0] = pack8(s, 0);
+          SLOT();
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 l4 = *reinterpret_cast<const float4*>(&Lt[P][32 * blk + 8 * g + 4 * hi]);
-          const float nl[4] = {l4.x, l4.y, l4.z, l4.w};
+        for (int u = 0; u < 8; ++u) {  // dV; the rest of P, then dS
+          const int mb = u & 3;
+          dv[mb] = mfma32(ta[u], pb[u >> 2], dv[mb]);
+          if (u + 3 < 8) ta[u + 3] = read_tr(ob + 16 * ((u + 3) >> 2) * D, otr, (u + 3) & 3);
+          else tb[u - 5] = read_tr(qb, otr, u - 5);
+          if (u < 2) exps(12 + 2 * u);
+          if (u == 2) pb[1] = pack8(s, 1);
+          if (u >= 3 && u < 7) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            s[4 * g + i] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + i], a.c, nl[i]));
-            dp[4 * g + i] *= s[4 * g + i];
+            for (int i = 4 * (u - 3); i < 4 * (u - 3) + 4; ++i) dp[i] *= s[i];
           }
+          if (u == 5) db[0] = pack8(dp, 0);
+          if (u == 7) db[1] = pack8(dp, 1);
+          SLOT();
         }
-        bf16x8 pb[2], db[2];
-        pack_ops(s, pb);
-        pack_ops(dp, db);
-        // dV^T += dO^T P, dK^T += Q^T dS over the block's 32 queries
 #pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2) {
-          const int o0 = 16 * (2 * blk + k2) * D;
-#pragma unroll
-          for (int mb = 0; mb < 4; ++mb) {
-            const i16x4 olo = lds_read_tr16(ot + o0 + tk[0][mb]), ohi = lds_read_tr16(ot + o0 + tk[1][mb]);
-            dv[mb] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(olo, ohi, 0, 1, 2, 3, 4, 5, 6, 7)), pb[k2], dv[mb]);
-          }
-#pragma unroll
-          for (int mb = 0; mb < 4; ++mb) {
-            const i16x4 qlo = lds_read_tr16(qt + o0 + tk[0][mb]), qhi = lds_read_tr16(qt + o0 + tk[1][mb]);
-            dk[mb] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(qlo, qhi, 0, 1, 2, 3, 4, 5, 6, 7)), db[k2], dk[mb]);
-          }
+        for (int u = 0; u < 8; ++u) {  // dK
+          const int mb = u & 3;
+          dk[mb] = mfma32(tb[u], db[u >> 2], dk[mb]);
+          if (u + 3 < 8) tb[u + 3] = read_tr(qb + 16 * ((u + 3) >> 2) * D, otr, (u + 3) & 3);
+          SLOT();
         }
       }
     }
