@@ -417,12 +417,15 @@ __global__ __launch_bounds__(NT) void xattn_kernel(XArgs a) {
       const bool lastst = s + 1 == nt;
       f32x16 sc[2];
       qk(kb, sc);
-      if (lastst && more) {
+      if (lastst) {
         // the item's last scores are formed: the next item's queries into
-        // registers (they were loaded at this item's start)
-        if (memw) __builtin_amdgcn_s_waitcnt(0);
+        // registers (they were loaded at this item's start).  The barrier is
+        // also for the run's last item: past it, waves 0-3 have read the
+        // previous item's outputs out of every staging area, and this item's
+        // outputs may be staged.
+        if (memw && more) __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_s_barrier();
-        read_q();
+        if (more) read_q();
       }
       if (t + 1 == nt && lv < nt * BN) mask_tail(sc, lv - t * BN);
       bf16x8 pop0[2], pop1[2];

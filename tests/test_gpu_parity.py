@@ -13,7 +13,7 @@ import pytest
 import oracle
 import paper_2609_18077_amd as vx
 from paper_2609_18077_amd import inputs
-from tests.gpu_util import (assert_lse, assert_parity, errors, lengths_dev, log, rope_of, spec_of, to_bits,
+from tests.gpu_util import (MAX_ABS, assert_lse, assert_parity, errors, lengths_dev, log, rope_of, spec_of, to_bits,
                             to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -532,6 +532,34 @@ def test_persistent_short_keys_sampled(w):
     assert_parity(ob[:, rows], ro, w.name)
     assert_lse(lse[:, :, rows], rl, w.name)
     assert _convex_bounds_ok(ob, v, lv, list(range(w.H)))
+
+
+@pytest.mark.parametrize("lk,lens", [(64, [50]), (192, [192]), (512, [71, 130])], ids=str)
+def test_short_keys_last_item_of_a_run(lk, lens):
+    """Every output row of the short-key kernel, twelve times over, where an
+    item takes one to three key tiles and so meets no step barrier: the last
+    item of a workgroup's run must not stage its outputs over the previous
+    item's, which other waves may still be storing.  Against a plain float32
+    attention of the same bf16 inputs (contract: max-abs 2e-2), bit-equal
+    between the runs."""
+    import torch
+
+    B, H, Lq = len(lens), 64 // len(lens), 16384
+    log(f"case short keys, last item of a run: B{B} H{H} Lq{Lq} Lk{lk} lens={lens}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(43)
+    q, k, v = (torch.randn((B, n, H, 128), generator=g, device="cuda").to(torch.bfloat16) for n in (Lq, lk, lk))
+    lv = lengths_dev(lens)
+    scale = float(np.float32(1 / np.sqrt(128)))
+    outs = [vx.attn_fwd(q, k, v, scale=scale, kv_valid_len=lv) for _ in range(12)]
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        for h in range(H):
+            s = q[b, :, h].float() @ k[b, :n, h].float().t().contiguous() * scale
+            ref = torch.softmax(s, 1) @ v[b, :n, h].float()
+            assert float((outs[0][b, :, h].float() - ref).abs().max()) <= MAX_ABS, (b, h)
+    for i, o in enumerate(outs[1:]):
+        assert torch.equal(o.view(torch.int16), outs[0].view(torch.int16)), i
 
 
 def test_batch_at_the_2gib_limit():
