@@ -18,6 +18,28 @@ inline hipError_t launch_kernel(void (*kernel)(A), unsigned grid, unsigned block
   return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(grid), dim3(block), args, 0, stream);
 }
 
+// Work split of the per-token kernels (rotation, norm): workgroups of 16
+// tokens.  With at least 1024 of them (4 per compute unit) the workgroups walk
+// the tokens and take all B * H rows of a token; with fewer, the rows are cut
+// into `parts` of `rows` (multiples of four, the loads in flight) so that about
+// 2048 workgroups exist.
+constexpr int kTokenGroup = 16;
+struct TokenSplit {
+  int parts, rows, grid;
+};
+inline TokenSplit token_split(int B, int L, int H) {
+  const int64_t groups = ((int64_t)L + kTokenGroup - 1) / kTokenGroup, rows = (int64_t)B * H;
+  TokenSplit s{1, (int)rows, 1024};
+  if (groups < 1024) {
+    int64_t parts = (2048 + groups - 1) / groups;
+    const int64_t most = (rows + 3) / 4;
+    if (parts > most) parts = most;
+    const int64_t per = (rows + parts * 4 - 1) / (parts * 4) * 4;
+    parts = (rows + per - 1) / per;
+    s = TokenSplit{(int)parts, (int)per, (int)(groups * parts)};
+  }
+  return s;
+}
 hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int B, int L, int H, const RopeParams& rp,
                          hipStream_t stream);
 // Compute units of the current device (queried once per device).

@@ -5,8 +5,9 @@
 // Layout as in the standalone rotary kernel: the 16 channel chunks (16 B)
 // of a (token, head) row go to 16 consecutive lanes; a lane holds the four
 // frequencies of its chunk, decodes its token's (t, h, w) once, forms the four
-// (cos, sin) pairs in registers and handles that chunk for every batch and
-// head of the token, four heads' loads in flight at a time.  A row's sum of
+// (cos, sin) pairs in registers and handles that chunk for the token's rows
+// (every batch and head; short sequences: a share of them), four rows' loads
+// in flight at a time, the first four before the angles.  A row's sum of
 // squares is combined across its 16 lanes with data-parallel lane moves
 // (rotations within the 16-lane row, then permutations within quads), so
 // each lane ends with the row total without touching LDS.  Every lane reads
@@ -21,7 +22,8 @@ namespace vidax {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTokensPerPass = kThreads / 16;
+constexpr int kTokensPerPass = kTokenGroup;
+static_assert(kTokensPerPass * 16 == kThreads, "16 lanes a token");
 
 struct QkNormArgs {
   const uint16_t* x;
@@ -29,6 +31,7 @@ struct QkNormArgs {
   const float* gain;  // [128] or null (unit gain)
   float eps;
   int B, L, H;
+  TokenSplit sp;
   RopeParams rp;
 };
 
@@ -86,11 +89,24 @@ __global__ __launch_bounds__(kThreads) void qk_norm_kernel(QkNormArgs a) {
       omega[p] = exp2f(-((float)(2 * j) / (float)da) * rp.log2_theta);
     }
   }
+  const float inv_d = 1.0f / kHeadDim;
+  const int r0 = (blockIdx.x % a.sp.parts) * a.sp.rows, r1 = min(r0 + a.sp.rows, a.B * a.H);
+  const int first = (blockIdx.x / a.sp.parts) * kTokensPerPass + (threadIdx.x >> 4);
+  const int stride = (gridDim.x / a.sp.parts) * kTokensPerPass;
+  const int b0 = r0 / a.H, b1 = (r1 - 1) / a.H;
   const size_t tok_stride = (size_t)a.H * kHeadDim;      // elements between tokens
   const size_t batch_stride = (size_t)a.L * tok_stride;  // elements between batches
-  const float inv_d = 1.0f / kHeadDim;
 
-  for (int n = blockIdx.x * kTokensPerPass + (threadIdx.x >> 4); n < a.L; n += gridDim.x * kTokensPerPass) {
+  for (int n = first; n < a.L; n += stride) {
+    const size_t row_n = (size_t)n * tok_stride + c * 8;  // the lane's chunk of the token's first row
+    uint4 v[4];
+    // rows past the last repeat it (their results are dropped)
+    auto load4 = [&](size_t row0, int h, int h1) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        v[u] = *reinterpret_cast<const uint4*>(a.x + row0 + (size_t)min(h + u, h1 - 1) * kHeadDim);
+    };
+    load4(b0 * batch_stride + row_n, r0 - b0 * a.H, min(r1 - b0 * a.H, a.H));
     const bool rot = ROPE && n < rp.n_rot;
     float cs[4] = {1.f, 1.f, 1.f, 1.f}, sn[4] = {0.f, 0.f, 0.f, 0.f};
     float hcs[8], hsn[8];  // half split: angle of each channel's pair
@@ -160,19 +176,16 @@ __global__ __launch_bounds__(kThreads) void qk_norm_kernel(QkNormArgs a) {
         }
         *reinterpret_cast<uint4*>(a.y + off) = make_uint4(o[0], o[1], o[2], o[3]);
     };
-    for (int b = 0; b < a.B; ++b) {
-      const size_t row0 = b * batch_stride + (size_t)n * tok_stride + c * 8;
-      int hh = 0;
-      for (; hh + 4 <= a.H; hh += 4) {
-        uint4 v[4];
+    for (int b = b0; b <= b1; ++b) {
+      const size_t row0 = b * batch_stride + row_n;
+      const int h0 = max(r0 - b * a.H, 0), h1 = min(r1 - b * a.H, a.H);
+      for (int h = h0; h < h1; h += 4) {
+        if (b > b0 || h > h0) load4(row0, h, h1);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const uint4*>(a.x + row0 + (size_t)(hh + u) * kHeadDim);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) put(v[u], row0 + (size_t)(hh + u) * kHeadDim);
-      }
-      for (; hh < a.H; ++hh) {
-        const size_t off = row0 + (size_t)hh * kHeadDim;
-        put(*reinterpret_cast<const uint4*>(a.x + off), off);
+        for (int u = 0; u < 4; ++u) {
+          if (h + u >= h1) break;  // uniform
+          put(v[u], row0 + (size_t)(h + u) * kHeadDim);
+        }
       }
     }
   }
@@ -182,13 +195,11 @@ __global__ __launch_bounds__(kThreads) void qk_norm_kernel(QkNormArgs a) {
 
 hipError_t launch_qk_norm(const uint16_t* x, uint16_t* y, const float* gain, float eps, int B, int L, int H,
                           const RopeParams& rp, hipStream_t stream) {
-  QkNormArgs a{x, y, gain, eps, B, L, H, rp};
-  int groups = (L + kTokensPerPass - 1) / kTokensPerPass;
-  int grid = groups < 1024 ? groups : 1024;  // 4 workgroups per CU
-  if (grid < 1) grid = 1;
-  if (!rp.enabled) return launch_kernel(qk_norm_kernel<false, false>, (unsigned)grid, (unsigned)kThreads, stream, a);
-  return rp.pair_mode ? launch_kernel(qk_norm_kernel<true, true>, (unsigned)grid, (unsigned)kThreads, stream, a)
-                      : launch_kernel(qk_norm_kernel<true, false>, (unsigned)grid, (unsigned)kThreads, stream, a);
+  const QkNormArgs a{x, y, gain, eps, B, L, H, token_split(B, L, H), rp};
+  const unsigned grid = (unsigned)a.sp.grid;
+  if (!rp.enabled) return launch_kernel(qk_norm_kernel<false, false>, grid, (unsigned)kThreads, stream, a);
+  return rp.pair_mode ? launch_kernel(qk_norm_kernel<true, true>, grid, (unsigned)kThreads, stream, a)
+                      : launch_kernel(qk_norm_kernel<true, false>, grid, (unsigned)kThreads, stream, a);
 }
 
 }  // namespace vidax

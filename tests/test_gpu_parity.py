@@ -114,6 +114,38 @@ def test_rope3d_matches_oracle(mode, inplace, heads):
     assert np.array_equal(to_bits(y)[:, 900:], x[:, 900:])
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("B,H,grid,L", [
+    (1, 1, (1, 1, 1), 1),      # one row
+    (1, 40, (1, 4, 4), 16),    # one token group, its rows over ten workgroups
+    (2, 5, (1, 5, 7), 40),     # a share of rows that crosses into the next batch; unrotated tokens
+    (3, 7, (2, 30, 30), 1801),  # 21 rows over five shares, the last of one row
+    (1, 2, (21, 30, 26), 16385),  # one token past 1024 groups: tokens walked with a stride
+], ids=str)
+def test_rope3d_and_norm_row_shares(mode, B, H, grid, L):
+    """The split of a token's (batch, head) rows over workgroups: rotation, its
+    transpose (in place) and the normalising prologue, every element."""
+    import torch
+
+    x = inputs.bf16_tensor(15, 0, (B, L, H, 128))
+    xf = oracle.bf16_bits_to_f64(x)
+    log(f"case row shares mode={mode} B={B} H={H} grid={grid} L={L}")
+    r, spec = vx.Rope(grid=grid, pair_mode=mode), oracle.RopeSpec(grid=grid, pair_mode=mode)
+    rows = np.arange(L)
+    y = vx.rope3d(to_dev(x), r)
+    ref = oracle.rope3d_ref(xf, spec)
+    assert np.all(np.abs(oracle.bf16_bits_to_f64(to_bits(y)) - ref) <= _rope_bound(xf, ref, spec, rows))
+    xd = to_dev(x)
+    vx.rope3d_transpose(xd, r, out=xd)
+    ref = oracle.rope_transpose_ref(xf, spec)
+    assert np.all(np.abs(oracle.bf16_bits_to_f64(to_bits(xd)) - ref) <= _rope_bound(xf, ref, spec, rows))
+    g = np.random.default_rng(16).uniform(0.5, 1.5, 128).astype(np.float32)
+    y = vx.qk_norm_rope(to_dev(x), r, gain=torch.from_numpy(g).cuda(), eps=1e-6)
+    ref = oracle.qk_norm_ref(xf, gain=g.astype(np.float64), eps=1e-6, rope=spec)
+    bound = _norm_bound(xf, g.astype(np.float64), 1e-6, ref, spec, rows)
+    assert np.all(np.abs(oracle.bf16_bits_to_f64(to_bits(y)) - ref) <= bound)
+
+
 def test_rope3d_full_size_wan13b():
     import torch
 
