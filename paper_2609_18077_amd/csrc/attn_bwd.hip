@@ -28,7 +28,6 @@
 // after batch, the XCDs of the longer batches finished last.
 #include <mutex>
 #include <type_traits>
-#include <utility>
 
 #include "launch.hpp"
 
@@ -119,19 +118,6 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& x, int k2) {
   for (int e = 0; e < 8; e += 2) w[e >> 1] = pack_bf16x2(x[8 * k2 + e], x[8 * k2 + e + 1]);
   return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
 }
-
-// f(0), ..., f(N - 1) with compile-time arguments.
-template <int N, typename F, int... I>
-__device__ __forceinline__ void for_slots_of(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>()), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void for_slots(F&& f) {
-  for_slots_of<N>(f, std::make_integer_sequence<int, N>());
-}
-
-// End of a slot of a hand-scheduled block: no instruction moves across it.
-#define SLOT() __builtin_amdgcn_sched_barrier(0)
 
 // Tile row (0..63) of register i of accumulator blk for lane half hi.
 [[maybe_unused]] __device__ __forceinline__ int acc_row(int blk, int i, int hi) { return 32 * blk + 8 * (i >> 2) + 4 * hi + (i & 3); }

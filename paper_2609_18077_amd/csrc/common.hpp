@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace vidax {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -48,21 +51,21 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Angle of table entry e: the entries of axis a are laid out [pos][j] with
-// d_a/2 entries per position; frequency theta^(-2j/d_a).
-__device__ __forceinline__ float2 rope_table_entry(const RopeParams& r, int e) {
-  int pos, j, da;
-  if (e < r.base1) {
-    int half = r.dt >> 1; pos = e / half; j = e - pos * half; da = r.dt;
-  } else if (e < r.base2) {
-    int half = r.dh >> 1; int f = e - r.base1; pos = f / half; j = f - pos * half; da = r.dh;
-  } else {
-    int half = r.dw >> 1; int f = e - r.base2; pos = f / half; j = f - pos * half; da = r.dw;
+// Fills the (cos, sin) table: entry base_a + pos * (d_a / 2) + j of axis a,
+// frequency theta^(-2j/d_a).  A thread keeps one channel pair (its frequency is
+// formed once, no division per entry) and takes every (nthreads / 64)-th position.
+__device__ __forceinline__ void build_rope_table(const RopeParams& r, float2* tab, int tid, int nthreads) {
+  const int pi = tid & 63, ht = r.dt >> 1, hh = r.dh >> 1;
+  int j, half, n, base;
+  if (pi < ht) { j = pi; half = ht; n = r.gt; base = 0; }
+  else if (pi < ht + hh) { j = pi - ht; half = hh; n = r.gh; base = r.base1; }
+  else { j = pi - ht - hh; half = r.dw >> 1; n = r.gw; base = r.base2; }
+  const float omega = exp2f(-((float)(2 * j) / (float)(2 * half)) * r.log2_theta);
+  for (int pos = tid >> 6; pos < n; pos += nthreads >> 6) {
+    float s, c;
+    sincosf((float)pos * omega, &s, &c);
+    tab[base + pos * half + j] = make_float2(c, s);
   }
-  float omega = exp2f(-((float)(2 * j) / (float)da) * r.log2_theta);
-  float s, c;
-  sincosf((float)pos * omega, &s, &c);
-  return make_float2(c, s);
 }
 
 // Table entry of channel pair `pi` (interleaved numbering, pi in [0, 64)) at
@@ -85,6 +88,19 @@ __host__ __device__ inline PairSlot pair_slot(const RopeParams& r, int pi) {
   }
   return s;
 }
+
+// f(0), ..., f(N - 1) with compile-time arguments.
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_slots_of(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_slots(F&& f) {
+  for_slots_of<N>(f, std::make_integer_sequence<int, N>());
+}
+
+// End of a slot of a hand-scheduled block: no instruction moves across it.
+#define SLOT() __builtin_amdgcn_sched_barrier(0)
 
 // Logical tile of workgroup i of n (n / B per batch, batch after batch).
 // Workgroups are dispatched round-robin over the 8 XCDs; each XCD gets a

@@ -20,7 +20,12 @@
 // the C input channels runs in stages of 64: each stage copies the W and x
 // tiles (256 rows x 64 channels each) straight from global memory into LDS,
 // double buffered, one barrier per stage; per stage a wave issues 32 matrix
-// instructions.  In LDS a tile row (128 bytes) is followed by 16 bytes of
+// instructions, one slot each with the operand reads of the next k-step; the
+// barrier stands before the last k-step (see run_stage).  32760 x 1536 -> 4608:
+// 447 -> 440 us from that schedule (3072 inputs: 870 -> 834), 440 -> 422 us from
+// the epilogue: bias as the accumulators' start, rotary table by pair columns
+// and only for q and k heads, three row pointers per token for its look-ups.
+// In LDS a tile row (128 bytes) is followed by 16 bytes of
 // padding: every copy instruction then fetches whole rows with its lanes in
 // address order (coalesced; the pad lane reads past the buffer's records:
 // zero, no memory access), and
@@ -134,63 +139,84 @@ __global__ __launch_bounds__(NT) void qkv_proj_kernel(QkvArgs a) {
     }
   };
 
+  // the accumulators start at the bias (register i of acc[cb][tb]: channel 32 cb
+  // + 8 (i >> 2) + 4 hi + (i & 3) of the wave's head), loaded beside the first copies
   f32x16 acc[4][2];
+  const bool live = n0 / D + wh < 3 * a.H;  // uniform: the wave's head exists
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) acc[cb][0] = acc[cb][1] = f32x16{};
-  // one stage: 4 k-steps x (4 channel blocks x 2 token blocks); the A operand
-  // of channel block cb, k-step st: row 128 wh + 32 cb + l32, chunk 2 st + hi
+  for (int cb = 0; cb < 4; ++cb) {
+    f32x16 x = f32x16{};
+    if (a.bias && live) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 bb = *reinterpret_cast<const float4*>(a.bias + n0 + wh * D + 32 * cb + 8 * g + 4 * hi);
+        x[4 * g] = bb.x; x[4 * g + 1] = bb.y; x[4 * g + 2] = bb.z; x[4 * g + 3] = bb.w;
+      }
+    }
+    acc[cb][0] = acc[cb][1] = x;
+  }
+  // One stage, hand-scheduled: 4 k-steps x (4 channel blocks x 2 token blocks),
+  // one slot per product; the slots of a k-step also issue the operand reads of
+  // the next one (two register sets).  The stage's barrier stands before its
+  // last k-step, whose operands are in registers by then: past it, this
+  // stage's buffers are free for the copies of stage s + 2, stage s + 1 is
+  // readable, and the last k-step's products cover the latency of its first
+  // operand reads.  The A operand of channel block cb, k-step st: row 128 wh +
+  // 32 cb + l32, chunk 2 st + hi.
   const int abase = (128 * wh + l32) * kPitch + 8 * hi;
   const int bbase = (64 * wt + l32) * kPitch + 8 * hi;
-  auto compute = [&](const uint16_t* wb, const uint16_t* xb) __attribute__((always_inline)) {
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      bf16x8 av[4], bv[2];
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-        av[cb] = *reinterpret_cast<const bf16x8*>(wb + abase + 32 * cb * kPitch + 16 * st);
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-        bv[tb] = *reinterpret_cast<const bf16x8*>(xb + bbase + 32 * tb * kPitch + 16 * st);
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) acc[cb][tb] = mfma32(av[cb], bv[tb], acc[cb][tb]);
-    }
+  bf16x8 av[2][4], bv[2][2];
+  // operand i (0, 1: token blocks; 2 .. 5: channel blocks) of k-step st into set t
+  auto read_op = [&](auto T, auto I, int st, const uint16_t* wb, const uint16_t* xb) __attribute__((always_inline)) {
+    constexpr int t = decltype(T)::value, i = decltype(I)::value;
+    if constexpr (i < 2) bv[t][i] = *reinterpret_cast<const bf16x8*>(xb + bbase + 32 * i * kPitch + 16 * st);
+    else av[t][i - 2] = *reinterpret_cast<const bf16x8*>(wb + abase + 32 * (i - 2) * kPitch + 16 * st);
   };
-
+  auto kstep = [&](auto T, int st_next, const uint16_t* wb, const uint16_t* xb) __attribute__((always_inline)) {
+    constexpr int t = decltype(T)::value;
+    for_slots<8>([&](auto I) __attribute__((always_inline)) {
+      constexpr int i = decltype(I)::value, cb = i >> 1, tb = i & 1;
+      acc[cb][tb] = mfma32(av[t][cb], bv[t][tb], acc[cb][tb]);
+      if constexpr (i < 6) read_op(std::integral_constant<int, 1 - t>(), I, st_next, wb, xb);
+      SLOT();
+    });
+  };
   const int ns = a.C / BK;
+  using set0 = std::integral_constant<int, 0>;
+  using set1 = std::integral_constant<int, 1>;
+  auto run_stage = [&](int s, uint16_t* wb, uint16_t* xb, uint16_t* wnext, uint16_t* xnext)
+      __attribute__((always_inline)) {
+    kstep(set0(), 1, wb, xb);
+    kstep(set1(), 2, wb, xb);
+    kstep(set0(), 3, wb, xb);
+    __builtin_amdgcn_s_waitcnt(0);  // the last k-step's operands; this wave's copies of stage s + 1
+    __syncthreads();
+    if (s + 2 < ns) stage(s + 2, wb, xb);
+    kstep(set1(), 0, wnext, xnext);  // (after the last stage: operands of no use)
+  };
   stage(0, W0, X0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  int s = 0;
-  for (; s + 1 < ns; s += 2) {
-    stage(s + 1, W1, X1);
-    compute(W0, X0);
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed
-    __syncthreads();
-    if (s + 2 < ns) stage(s + 2, W0, X0);
-    compute(W1, X1);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+  if (ns > 1) stage(1, W1, X1);
+  for_slots<6>([&](auto I) __attribute__((always_inline)) { read_op(set0(), I, 0, W0, X0); });
+  for (int s = 0; s < ns; s += 2) {
+    run_stage(s, W0, X0, W1, X1);
+    if (s + 1 < ns) run_stage(s + 1, W1, X1, W0, X0);
   }
-  if (s < ns) {
-    compute(W0, X0);
-    __syncthreads();
-  }
+  __syncthreads();  // the stage buffers are free for the epilogue
 
   // ---- epilogue.  Register i of acc[cb][tb] holds channel 32 cb + 8 (i >> 2)
   // + 4 hi + (i & 3) of the wave's head, token m0 + 64 wt + 32 tb + l32.
   const RopeParams& rp = a.rp;
   float2* tab = reinterpret_cast<float2*>(W0);  // the stage buffers are free now (36 KB)
-  if (rp.enabled) {
-    for (int e = tid; e < rp.n_entries; e += NT) tab[e] = rope_table_entry(rp, e);
+  if (rp.enabled && n0 / D < 2 * a.H) {  // uniform: value heads are not rotated
+    build_rope_table(rp, tab, tid, NT);
     __syncthreads();
   }
   const int hg = n0 / D + wh;        // global head index over q, k, v
-  if (hg >= 3 * a.H) return;         // uniform: past the last head (no barrier follows)
+  if (!live) return;                 // past the last head (no barrier follows)
   const int part = hg / a.H, head = hg - part * a.H;
   uint16_t* outp = a.out[part];
-  const int chan0 = hg * D;          // first row of this head in W
 
   const float* gain = part == 0 ? a.gain_q : a.gain_k;
   // the wave's 8 KB output staging area (32 tokens x 128 channels), in the
@@ -201,19 +227,6 @@ __global__ __launch_bounds__(NT) void qkv_proj_kernel(QkvArgs a) {
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     const int m = m0 + 64 * wt + 32 * tb + l32;
-    // bias (4 consecutive channels per (cb, g), one 16-byte load)
-    if (a.bias) {
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 bb = *reinterpret_cast<const float4*>(a.bias + chan0 + 32 * cb + 8 * g + 4 * hi);
-          acc[cb][tb][4 * g + 0] += bb.x;
-          acc[cb][tb][4 * g + 1] += bb.y;
-          acc[cb][tb][4 * g + 2] += bb.z;
-          acc[cb][tb][4 * g + 3] += bb.w;
-        }
-    }
     if (part < 2) {
       float ss = 0.f;
 #pragma unroll
@@ -291,14 +304,20 @@ __global__ __launch_bounds__(NT) void qkv_proj_kernel(QkvArgs a) {
         const int rr = n - t * rp.gh * rp.gw;
         const int hh = rr / rp.gw;
         const int ww = rr - hh * rp.gw;
+        // table entry of pair pi: pi + a value of its axis (the lane's pairs
+        // are 2 hi past the constant ones of the loop)
+        const int ht = rp.dt >> 1, hd = rp.dh >> 1;
+        const int end_t = ht - 2 * hi, end_h = ht + hd - 2 * hi;
+        const float2* const tab_t = tab + t * ht + 2 * hi;
+        const float2* const tab_h = tab + rp.base1 - ht + hh * hd + 2 * hi;
+        const float2* const tab_w = tab + rp.base2 - ht - hd + ww * (rp.dw >> 1) + 2 * hi;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
           for (int i = 0; i < 16; i += 2) {
-            const int c = 32 * cb + 8 * (i >> 2) + 4 * hi + (i & 3);  // even: pair c / 2
-            const PairSlot sl = pair_slot(rp, c >> 1);
-            const int pos = sl.axis == 0 ? t : (sl.axis == 1 ? hh : ww);
-            const float2 e = tab[sl.base + pos * sl.stride];
+            // channel 32 cb + 8 (i >> 2) + 4 hi + (i & 3), even
+            const int pi = 16 * cb + 4 * (i >> 2) + ((i & 3) >> 1);
+            const float2 e = (pi < end_t ? tab_t : (pi < end_h ? tab_h : tab_w))[pi];
             const float x0 = acc[cb][tb][i], x1 = acc[cb][tb][i + 1];
             acc[cb][tb][i] = fmaf(x0, e.x, -x1 * e.y);
             acc[cb][tb][i + 1] = fmaf(x0, e.y, x1 * e.x);
