@@ -122,20 +122,6 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& x, int k2) {
 // Tile row (0..63) of register i of accumulator blk for lane half hi.
 [[maybe_unused]] __device__ __forceinline__ int acc_row(int blk, int i, int hi) { return 32 * blk + 8 * (i >> 2) + 4 * hi + (i & 3); }
 
-// Own row `row` of the wave (lane holds it), d = 32 mb + 8 g + 4 hi + (0..3):
-// acc^T * mul -> bf16, 8-byte stores.
-__device__ __forceinline__ void store_own(uint16_t* p, const f32x16 acc[4], float mul, int hi) {
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint2 pk;
-      pk.x = pack_bf16x2(acc[mb][4 * g + 0] * mul, acc[mb][4 * g + 1] * mul);
-      pk.y = pack_bf16x2(acc[mb][4 * g + 2] * mul, acc[mb][4 * g + 3] * mul);
-      *reinterpret_cast<uint2*>(p + mb * 32 + 8 * g + 4 * hi) = pk;
-    }
-}
-
 // ---- dQ: one tile of 32 NWQ queries of one (b, h) per workgroup of NWQ
 // waves: 8 for long key sequences, 4 for short ones (two workgroups then
 // share a CU, so that one's start and end overlap the other's products --
@@ -205,17 +191,73 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
   const int lv = valid_keys(a, b);
   const int qrow = qt * BWQ + wave * 32 + l32;
   const bool qlive = qrow < a.Lq;
-  const size_t rowoff = ((size_t)b * a.Lq + (qlive ? qrow : 0)) * tok + (size_t)h * D;
-  uint16_t* dqp = a.dq + rowoff;
   const size_t lrow = ((size_t)b * a.H + h) * a.Lq + (qlive ? qrow : 0);
-  bf16x8 dop[8];
-  own_operand(a.dout + rowoff, qlive, hi, dop);
+  // The wave's 32 rows come in and go out whole (16 lanes a 256-byte row),
+  // through 8 KB staging areas in the tile buffers, free before the first
+  // copies and after the last tile: one per wave, or with 4 waves two (q and
+  // dO at once).  Per-lane 16-byte pieces of 32 rows would fetch every line
+  // several times: at short key sequences these rows are most of the traffic
+  // (2 x 40 heads x 32760 x 512: backward 1696 -> 1602 us).
+  constexpr int AREAS = 8 / NWQ;
+  const int wa = AREAS * wave;
+  uint16_t* const area = (wa < 2 ? K0 : wa < 4 ? K1 : wa < 6 ? V0 : V1) + (wa & 1) * 32 * D;
+  const int row0 = qt * BWQ + wave * 32;
+  const size_t off0 = ((size_t)b * a.Lq + row0) * tok + (size_t)h * D;  // first row (may lie past Lq: no records then)
+  auto rows_rsrc = [&](const uint16_t* base) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(base + off0), (short)0, __builtin_amdgcn_readfirstlane(min(max(a.Lq - row0, 0), 32) * rbytes), kBufferFlags);
+  };
+  // rows 4 i .. 4 i + 3: byte offset of what the lane moves (position lane & 15 of row 4 i + (lane >> 4))
+  auto row_off = [&](int i) __attribute__((always_inline)) {
+    const int r = 4 * i + (lane >> 4);
+    return r * rbytes + ((lane & 15) ^ swz(r)) * 16;
+  };
+  auto rows_in = [&](const uint16_t* base, uint16_t* dst) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs = rows_rsrc(base);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(dst + 4 * i * D), 16, row_off(i), 0, 0, 0);
+  };
+  const TileOffsets off = tile_offsets(lane);
+  auto own_rows = [&](const uint16_t* src, bf16x8 op[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) op[s] = read_row(src, off.row, s);
+  };
+  // dQ = acc * mul, row l32, d = 32 mb + 8 g + 4 hi .. + 3: half hi of chunk 4 mb + g
+  auto rows_out = [&](const f32x16 acc[4], float mul) __attribute__((always_inline)) {
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        uint2 pk;
+        pk.x = pack_bf16x2(acc[mb][4 * g + 0] * mul, acc[mb][4 * g + 1] * mul);
+        pk.y = pack_bf16x2(acc[mb][4 * g + 2] * mul, acc[mb][4 * g + 3] * mul);
+        *reinterpret_cast<uint2*>(area + l32 * D + ((4 * mb + g) ^ swz(l32)) * 8 + 4 * hi) = pk;
+      }
+    const __amdgpu_buffer_rsrc_t rs = rows_rsrc(a.dq);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(area + (4 * i + (lane >> 4)) * D + (lane & 15) * 8);
+      __builtin_amdgcn_raw_buffer_store_b128(v, rs, row_off(i), 0, 0);  // rows past Lq: past the records, dropped
+    }
+  };
+  bf16x8 dop[8], qop[8], oop[8];
+  rows_in(a.dout, area);
+  if (AREAS == 2) rows_in(a.q, area + 32 * D);
+  own_operand(a.o + ((size_t)b * a.Lq + (qlive ? qrow : 0)) * tok + (size_t)h * D, qlive, hi, oop);
+  const float lse2 = qlive ? a.lse[lrow] * kLog2e : INFINITY;  // dead rows: P = 0
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's rows have landed
+  own_rows(area, dop);
+  if (AREAS == 2) {
+    own_rows(area + 32 * D, qop);
+  } else {
+    __builtin_amdgcn_s_waitcnt(0);  // dO is out of the area
+    rows_in(a.q, area);
+  }
   // D of the own row: this lane half's 64 products <dO, O>, then the other
   // half's; stored for the dkdv kernel (every row, also without valid keys)
   float dl;
   {
-    bf16x8 oop[8];
-    own_operand(a.o + rowoff, qlive, hi, oop);
     // packed bf16 pair products, two fp32 chains
     float sum[2] = {0.f, 0.f};
 #pragma unroll
@@ -230,16 +272,19 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
     dl = half_sum(sum[0] + sum[1]);
     if (qlive && hi == 0) a.delta[lrow] = dl;
   }
+  if (AREAS == 1) {
+    __builtin_amdgcn_s_waitcnt(0);
+    own_rows(area, qop);
+  }
   f32x16 acc[4];
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x16{};
+  __builtin_amdgcn_s_waitcnt(0);  // the rows are out of the staging areas
+  __syncthreads();
   if (lv == 0) {  // no valid key: dQ = 0
-    if (qlive) store_own(dqp, acc, 0.f, hi);
+    rows_out(acc, 0.f);
     return;
   }
-  bf16x8 qop[8];
-  own_operand(a.q + rowoff, qlive, hi, qop);
-  const float lse2 = qlive ? a.lse[lrow] * kLog2e : INFINITY;  // dead rows: P = 0
 
   const uint16_t* kbh = a.k + (size_t)b * a.Lk * tok + (size_t)h * D;
   const uint16_t* vbh = a.v + (size_t)b * a.Lk * tok + (size_t)h * D;
@@ -260,7 +305,6 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr)(vb + (NCOPY * wave + u) * 512), 16, cg[u], 0, 0, 0);
     }
   };
-  const TileOffsets off = tile_offsets(lane);
   copies(0, K0, V0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -348,7 +392,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
   } else {
     step(even(), last(), j);
   }
-  if (qlive) store_own(dqp, acc, a.scale, hi);
+  __syncthreads();  // every wave is done with the last tile
+  rows_out(acc, a.scale);
 }
 
 // 4 waves (128 queries) a workgroup where the key sequence is short, 8
