@@ -34,10 +34,11 @@ HIPCC_FLAGS = [
 ]
 
 
-# Per-source compiler flags.  The forward attention kernel is scheduled with
+# Per-source compiler flags.  The forward attention kernels are scheduled with
 # LLVM's instruction-level-parallelism strategy (about 0.5 % faster at the
 # benchmark shape); the other kernels are slower with it, so it is not global.
 SOURCE_FLAGS = {
+    "attn_fwd_split.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "attn_fwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }
 

@@ -322,6 +322,62 @@ def test_prerotated_keys(w):
     assert_lse(l.cpu().numpy(), rl, f"{w.name} prerotated")
 
 
+@pytest.mark.parametrize("mode", ["none", "fused", "prerotated", "half"])
+@pytest.mark.parametrize("Lq,lens", [
+    (129, [1, 32, 33, 64, 0]),        # the second key group without keys, with one key, with a full tile
+    (520, [65, 96, 97, 128, 129]),    # two and three steps; a ragged tile in either group
+    (513, [200, 256, 320, 513, 520]),  # four to nine steps: every place where the steps can stop
+], ids=str)
+def test_two_key_groups(mode, Lq, lens):
+    """The kernel of launches with few query tiles (128 rows, alternate 32-key
+    tiles to two groups, merged at the end): valid lengths at the edges of the
+    groups' tiles and of its four-buffer loop, in every rotation mode; text
+    tokens past the grid; and a launch one workgroup past its limit, which the
+    256-row kernel takes."""
+    import dataclasses
+
+    import torch
+
+    Lk = 520
+    w = inputs.custom(f"groups_{mode}", B=len(lens), H=2, Lq=Lq, Lk=Lk, seed=51,
+                      grid=None if mode == "none" else (2, 8, 8), kv_valid=("fixed", lens))
+    q, k, v, lv = inputs.make_qkv(w)
+    log(f"case two key groups {mode} Lq{Lq} lens={lens}")
+    dec = oracle.bf16_bits_to_f64
+    r, spec, kd = rope_of(w), spec_of(w), to_dev(k)
+    if mode in ("prerotated", "half"):
+        r, spec = (dataclasses.replace(x, pair_mode=1 if mode == "half" else 0) for x in (r, spec))
+        kd = vx.rope3d(kd, r)
+        r = dataclasses.replace(r, keys_prerotated=True)
+    o, l = vx.attn_fwd(to_dev(q), kd, to_dev(v), scale=w.scale, kv_valid_len=lengths_dev(lv), rope=r, return_lse=True)
+    torch.cuda.synchronize()
+    ro, rl = oracle.attn_ref(dec(q), dec(k), dec(v), w.scale, kv_valid_len=lv, rope=spec, workers=8)
+    assert_parity(to_bits(o), ro, w.name)
+    assert_lse(l.cpu().numpy(), rl, w.name)
+
+
+def test_two_key_groups_agree_with_the_dense_kernel():
+    """The same head in a launch of 128 rows x 2 heads (two key groups) and
+    among 260 heads (one workgroup of 128 rows too many: the 256-row kernel):
+    the results differ by roundings of P and of the output only."""
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(53)
+    q, k, v = (torch.randn((1, n, 260, 128), generator=g, device="cuda").to(torch.bfloat16) for n in (100, 600, 600))
+    log("case two key groups against the dense kernel")
+    dense, ld = vx.attn_fwd(q, k, v, return_lse=True)
+    few, lf = vx.attn_fwd(*(x[:, :, :2].contiguous() for x in (q, k, v)), return_lse=True)
+    torch.cuda.synchronize()
+    a, b = few.float(), dense[:, :, :2].float()
+    assert float((a - b).norm() / b.norm()) <= 1e-2
+    assert float((a - b).abs().max()) <= MAX_ABS
+    # each row sum adds p rounded to bf16 (relative error at most 2^-9 each, of
+    # different roundings where the reference differs): ln of it is off by at
+    # most 2^-9 on either side
+    assert float((lf - ld[:, :2]).abs().max()) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("w", [inputs.WORKLOADS["tiny"], RAGGED[0], RAGGED[5]], ids=lambda w: w.name)
 def test_half_split_pairs_prerotated_keys(w):
     """Half-split pairs (channel o_a + j with o_a + j + d_a/2): k rotated by
