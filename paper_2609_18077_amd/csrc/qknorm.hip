@@ -100,13 +100,23 @@ __global__ __launch_bounds__(kThreads) void qk_norm_kernel(QkNormArgs a) {
   for (int n = first; n < a.L; n += stride) {
     const size_t row_n = (size_t)n * tok_stride + c * 8;  // the lane's chunk of the token's first row
     uint4 v[4];
-    // rows past the last repeat it (their results are dropped)
     auto load4 = [&](size_t row0, int h, int h1) __attribute__((always_inline)) {
+      if (h + 4 <= h1) {  // uniform
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const uint4*>(a.x + row0 + (size_t)(h + u) * kHeadDim);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+          if (h + u < h1) v[u] = *reinterpret_cast<const uint4*>(a.x + row0 + (size_t)(h + u) * kHeadDim);
+      }
+    };
+    {  // the first rows, before the angles, without a branch: a row past the last repeats it
+      const size_t row0 = b0 * batch_stride + row_n;
+      const int h = r0 - b0 * a.H, h1 = min(r1 - b0 * a.H, a.H);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         v[u] = *reinterpret_cast<const uint4*>(a.x + row0 + (size_t)min(h + u, h1 - 1) * kHeadDim);
-    };
-    load4(b0 * batch_stride + row_n, r0 - b0 * a.H, min(r1 - b0 * a.H, a.H));
+    }
     const bool rot = ROPE && n < rp.n_rot;
     float cs[4] = {1.f, 1.f, 1.f, 1.f}, sn[4] = {0.f, 0.f, 0.f, 0.f};
     float hcs[8], hsn[8];  // half split: angle of each channel's pair
