@@ -68,6 +68,7 @@ struct BwdArgs {
   // reduce kernel sums them
   int qsplit, qper;
   float* part;
+  int kper;  // keys per workgroup of the dkdv kernel (kBwdKeys or half of it)
 };
 
 [[maybe_unused]] __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -419,7 +420,12 @@ __global__ __launch_bounds__(512) void bwd_dq8_kernel(BwdArgs a) { dq_body<8>(a)
 // it reaches another column, and the column is written as zero.
 // A workgroup with at most 128 valid keys gives each of its 32-key groups to
 // two waves, which take alternate query blocks and add up at the end (short
-// texts would leave more than half of the waves idle).
+// texts would leave more than half of the waves idle).  So does every workgroup
+// of a launch whose 128-key tiles still fit the compute units in one round
+// (unsplit): half the chain per workgroup and no partials.  Whole
+// call with forward and rotations, against runs of 2 query tiles: 2 heads x 512
+// tokens 84.2 -> 79.6 us, 12 x 510 82.0 -> 79.5; forward and backward of 80 x
+// 500 queries x 300 keys 68.4 -> 57.8.
 constexpr int BK = kBwdKeys;  // keys per workgroup
 constexpr int KOWN = 32 * D;  // elements of one wave's own keys in LDS
 
@@ -436,7 +442,8 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
   const int h = bh % a.H, b = bh / a.H;
   const int tok = a.H * D, rbytes = tok * 2;
   const int lv = valid_keys(a, b);
-  const int nvalid = lv - kt * BK;  // valid keys of this workgroup (may be past BK, or negative)
+  const int key0 = kt * a.kper;
+  const int nvalid = lv - key0;  // valid keys from the workgroup's first on (may be past its own, or negative)
   const int t0 = sp * a.qper;
   const int t1 = min(t0 + a.qper, (a.Lq + BN - 1) / BN);
   f32x16 dk[4], dv[4];
@@ -482,12 +489,12 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
     }
   };
   if (nvalid <= 0 || t0 >= t1) {  // no valid key (zero gradient) or no query in this run
-    finish(kt * BK + wave * 32 + l32);
+    if (wave * 32 < a.kper) finish(key0 + wave * 32 + l32);
     return;
   }
-  const bool paired = nvalid <= BK / 2;  // uniform: two waves per 32-key group
+  const bool paired = nvalid <= BK / 2 || a.kper < BK;  // uniform: two waves per 32-key group
   const int kg = paired ? wave & 3 : wave, part = wave >> 2;
-  const int krow = kt * BK + kg * 32 + l32;
+  const int krow = key0 + kg * 32 + l32;
   const bool wlive = kg * 32 < nvalid;  // uniform
   const bool klive = krow < a.Lk;
   // own k and v as B operands: lane holds key krow, chunk 2 st + hi; k goes to LDS
@@ -650,7 +657,7 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
     }
     __syncthreads();
     if (part == 1) {
-      finish(krow + BK / 2);  // the upper half of the tile holds no valid key: zero
+      if (a.kper == BK) finish(krow + BK / 2);  // the upper half of the tile holds no valid key: zero
       return;
     }
 #pragma unroll
@@ -727,6 +734,7 @@ hipError_t launch_attn_bwd(const uint16_t* q, const uint16_t* k, const uint16_t*
   a.qsplit = sp.qsplit;
   a.qper = sp.qper;
   a.part = sp.qsplit > 1 ? ws + sp.part_offset : nullptr;
+  a.kper = BK;
   hipError_t e = hipSuccess;
   if (Lq > 0) {
     const bool short_keys = (Lk + BN - 1) / BN <= kDqShortTiles;
@@ -738,7 +746,9 @@ hipError_t launch_attn_bwd(const uint16_t* q, const uint16_t* k, const uint16_t*
     if (e != hipSuccess) return e;
   }
   if (Lk > 0) {
-    a.ntile = (Lk + BK - 1) / BK;
+    const bool few = a.qsplit == 1 && (int64_t)((Lk + BK / 2 - 1) / (BK / 2)) * B * H <= device_cu_count();
+    a.kper = few ? BK / 2 : BK;
+    a.ntile = (Lk + a.kper - 1) / a.kper;
     a.nwg = a.ntile * B * H * a.qsplit;
     e = launch_kernel(bwd_dkdv_kernel, (unsigned)a.nwg, (unsigned)NT, stream, a);
     if (e != hipSuccess) return e;

@@ -48,9 +48,10 @@ int device_cu_count();
 // Query-stream split of the backward's key-side kernel.  Its workgroups own
 // kBwdKeys keys of one (b, h), one workgroup per compute unit, and stream
 // every query in 64-row tiles; where there are fewer of them than twice the
-// compute units, the query tiles may be cut into qsplit runs of qper tiles
-// (at least 2 tiles a run, at most 32 runs).  Chosen: the least time in units
-// of one tile's (about 3.6 us): rounds x (tiles a run + 2 for a workgroup's
+// compute units and more than 8 query tiles, the tiles may be cut into qsplit
+// runs of qper tiles (at least 2 tiles a run, at most 32 runs; up to 8
+// tiles, 128-key workgroups without a split were faster by 3 to 22%).  Chosen: the least time in
+// units of one tile's (about 3.6 us): rounds x (tiles a run + 2 for a workgroup's
 // start and end), and for a split 3 for the extra launch and the bytes of the
 // fp32 partials (written and read: 16 bytes a gradient value and run, about
 // 14 MB in a tile's time).  The partial dK and dV of the runs follow D in the
@@ -69,7 +70,7 @@ inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus) {
   const int qtiles = (Lq + kRows - 1) / kRows;
   const int64_t nkv = (int64_t)((Lk + kBwdKeys - 1) / kBwdKeys) * B * H;
   r.qsplit = 1;
-  if (nkv > 0 && nkv < 2 * (int64_t)cus) {
+  if (nkv > 0 && nkv < 2 * (int64_t)cus && qtiles > 8) {
     const double part = (double)B * Lk * H * kHeadDim * 16 / 14e6;
     double best = 0;
     for (int s = 1; s <= 32 && (s == 1 || s <= qtiles / 2); ++s) {

@@ -140,6 +140,18 @@ def test_attn_bwd_key_groups(Lq, Lk, lens):
     _bwd_case(inputs.custom("bwd_keys", B=3, H=2, Lq=Lq, Lk=Lk, seed=39, kv_valid=("fixed", lens)))
 
 
+@pytest.mark.parametrize("H,Lq,Lk,lens", [
+    (42, 130, 256, [97, 255, 256]),    # 252 workgroups of 128 keys: two waves a 32-key group
+    (43, 130, 256, [127, 128, 256]),   # 258 would not fit 256 units at once: 256 keys each
+    (26, 65, 385, [128, 257, 385]),    # 128-key tiles past 256 units, a tile of one key
+    (17, 200, 513, [129, 384, 513]),   # 5 tiles of 128 keys, the last of one key
+], ids=str)
+def test_attn_bwd_half_key_workgroups(H, Lq, Lk, lens):
+    """Both sides of the rule that gives the key-side kernel 128-key
+    workgroups, with valid lengths at the edges of either's tiles."""
+    _bwd_case(inputs.custom("bwd_half", B=3, H=H, Lq=Lq, Lk=Lk, seed=40, kv_valid=("fixed", lens)))
+
+
 def _random_bwd_shapes(n=10, seed=2027):
     """Seeded random shapes: batches, heads, query and key counts off the
     256-row and 64-row tile grids, per-batch valid lengths from 0 to past Lk
