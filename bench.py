@@ -58,7 +58,7 @@ def algorithmic_bytes(w, lv):
     return float(2 * w.B * w.Lq * row + 2 * int(lvs.sum()) * row)
 
 
-FWD_SOURCES = ("attn_fwd.hip", "xattn_fwd.hip", "attn_tile.hpp", "common.hpp")
+FWD_SOURCES = ("attn_fwd.hip", "attn_fwd_split.hip", "xattn_fwd.hip", "attn_args.hpp", "attn_tile.hpp", "common.hpp")
 
 
 def kernel_source_digest():
