@@ -13,32 +13,55 @@ namespace vidax {
 // alone (an error left behind by an earlier, unrelated HIP call is not
 // reported as this launch's failure, as hipGetLastError would).
 template <typename A>
-inline hipError_t launch_kernel(void (*kernel)(A), unsigned grid, unsigned block, hipStream_t stream, A arg) {
+inline hipError_t launch_kernel(void (*kernel)(A), dim3 grid, unsigned block, hipStream_t stream, A arg) {
   void* args[] = {&arg};
-  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(grid), dim3(block), args, 0, stream);
+  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(block), args, 0, stream);
 }
 
 // Work split of the per-token kernels (rotation, norm): workgroups of 16
-// tokens.  With at least 1024 of them (4 per compute unit) the workgroups walk
-// the tokens and take all B * H rows of a token; with fewer, the rows are cut
-// into `parts` of `rows` (multiples of four, the loads in flight) so that about
-// 2048 workgroups exist.
+// tokens, gx x gy x gz of them.  Workgroup (x, y, z) takes heads x * rows ..
+// + rows - 1 of batches z * nb .. + nb - 1 for every gy-th group of tokens.
+// Every share of a token's rows forms the token's angles anew.  Up to 320 groups
+// (about a workgroup per compute unit) the launch is one workgroup's chain over
+// its rows, four at a time: shares of four rows as far as 1024 workgroups, or of
+// eight as far as 2048, where they halve that chain.  Past that a compute unit
+// has another workgroup beside one that waits: equal shares of 12 rows or of 8,
+// as far as 2560 workgroups (unequal ones leave units idle: 7800 tokens x 40
+// heads 26.5 us unshared, 25.8 in shares of 8, 28.9 in shares of 12, 12, 12 and
+// 4).  Half-split norm: 4680 x 12 11.4 us unshared and 10.3 in three shares, but
+// 7800 x 12 12.8 and 13.5 in two; 7800 x 24 20.1 and 18.7.
 constexpr int kTokenGroup = 16;
 struct TokenSplit {
-  int parts, rows, grid;
+  int rows, nb;
+  int gx, gy, gz;
 };
 inline TokenSplit token_split(int B, int L, int H) {
-  const int64_t groups = ((int64_t)L + kTokenGroup - 1) / kTokenGroup, rows = (int64_t)B * H;
-  TokenSplit s{1, (int)rows, 1024};
-  if (groups < 1024) {
-    int64_t parts = (2048 + groups - 1) / groups;
-    const int64_t most = (rows + 3) / 4;
-    if (parts > most) parts = most;
-    const int64_t per = (rows + parts * 4 - 1) / (parts * 4) * 4;
-    parts = (rows + per - 1) / per;
-    s = TokenSplit{(int)parts, (int)per, (int)(groups * parts)};
+  const int64_t groups = ((int64_t)L + kTokenGroup - 1) / kTokenGroup;
+  TokenSplit s{H, B, 1, (int)(groups < 1024 ? groups : 1024), 1};
+  if (groups >= 1024) return s;  // the workgroups walk the tokens
+  const int64_t all = (int64_t)B * H;
+  auto cut = [&](int gx, int gz) {  // about gx x gz shares, the heads in multiples of four
+    TokenSplit c = s;
+    c.rows = gx > 1 ? (H + gx * 4 - 1) / (gx * 4) * 4 : H;
+    c.nb = (B + gz - 1) / gz;
+    c.gx = (H + c.rows - 1) / c.rows;
+    c.gz = (B + c.nb - 1) / c.nb;
+    return c;
+  };
+  if (groups > 320) {
+    const int gx = H < 24 ? 1 : H % 12 == 0 ? H / 12 : H % 8 == 0 ? H / 8 : 1;
+    int nb = 1;  // of every batch, or of as many at a time as the limits ask for
+    while (nb < B && (B % nb != 0 || (int64_t)nb * H < 12 || groups * gx * (B / nb) > 2560)) ++nb;
+    return groups * gx * (B / nb) <= 2560 ? cut(gx, B / nb) : s;
   }
-  return s;
+  const int64_t fours = groups <= 128 ? (all + 3) / 4 : all / 4;  // up to 128: the last one may be smaller
+  const int64_t fine = 1024 / groups < fours ? 1024 / groups : fours;
+  const int64_t coarse = 2048 / groups < all / 8 ? 2048 / groups : all / 8;
+  const int parts = (int)(fine > coarse ? fine : coarse);
+  if (parts < 2) return s;
+  const TokenSplit c = parts > B ? cut((groups <= 128 ? parts + B - 1 : parts) / B, B) : cut(1, parts);
+  auto chain = [](const TokenSplit& t) { return ((int64_t)t.rows * t.nb + 3) / 4; };
+  return 2 * chain(c) <= chain(s) ? c : s;
 }
 hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int B, int L, int H, const RopeParams& rp,
                          hipStream_t stream);

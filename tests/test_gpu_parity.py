@@ -118,8 +118,11 @@ def test_rope3d_matches_oracle(mode, inplace, heads):
 @pytest.mark.parametrize("B,H,grid,L", [
     (1, 1, (1, 1, 1), 1),      # one row
     (1, 40, (1, 4, 4), 16),    # one token group, its rows over ten workgroups
-    (2, 5, (1, 5, 7), 40),     # a share of rows that crosses into the next batch; unrotated tokens
-    (3, 7, (2, 30, 30), 1801),  # 21 rows over five shares, the last of one row
+    (2, 5, (1, 5, 7), 40),     # shares of four heads and of one, in either batch; unrotated tokens
+    (5, 3, (1, 5, 7), 40),     # shares of two batches, the last of one; rows in flight across batches
+    (1, 11, (1, 17, 9), 161),  # shares of four, four and three heads
+    (3, 7, (2, 30, 30), 1801),  # shares of four heads and of three, in every batch
+    (1, 24, (7, 23, 32), 5153),  # past 320 groups of tokens: two shares of twelve heads
     (1, 2, (21, 30, 26), 16385),  # one token past 1024 groups: tokens walked with a stride
 ], ids=str)
 def test_rope3d_and_norm_row_shares(mode, B, H, grid, L):

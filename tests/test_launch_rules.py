@@ -1,0 +1,87 @@
+"""The host rules that choose a launch's shape (launch.hpp), compiled for the
+host and called directly: no GPU is needed.  What they must never get wrong
+(every row covered once, a workspace that is not overrun), and which side of a
+measured line a shape falls on."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+SOURCE = r"""
+#include "launch.hpp"
+using namespace vidax;
+extern "C" void token_rule(int B, int L, int H, int* out) {
+  const TokenSplit s = token_split(B, L, H);
+  out[0] = s.rows; out[1] = s.nb; out[2] = s.gx; out[3] = s.gy; out[4] = s.gz;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc is not available")
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "librules.so"
+    src.write_text(SOURCE)
+    res = subprocess.run([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared",
+                          "-x", "hip", "-I", os.path.join(ROOT, "paper_2609_18077_amd", "csrc"), str(src), "-o",
+                          str(lib)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-4000:]
+    return ctypes.CDLL(str(lib))
+
+
+def _token(rules, B, L, H):
+    out = (ctypes.c_int * 5)()
+    rules.token_rule(B, L, H, out)
+    return list(out)
+
+
+def _token_shapes():
+    rng = np.random.default_rng(61)
+    edges = [(1, 1, 1), (1, 16, 40), (1, 40, 5), (2, 40, 5), (5, 40, 3), (1, 901, 11), (2, 901, 13), (64, 520, 1),
+             (1, 5120, 24), (1, 5121, 24), (1, 16384, 7), (1, 16385, 7), (33, 8200, 3), (2000, 16, 1), (1, 16, 5000)]
+    return edges + [(int(rng.integers(1, 40)), int(np.exp(rng.uniform(0, 11))), int(rng.integers(1, 60)))
+                    for _ in range(300)]
+
+
+def test_token_split_covers_every_row_once(rules):
+    """Workgroup (x, y, z): heads x * rows .. of batches z * nb .., every gy-th
+    group of 16 tokens.  No share is empty, none is missing."""
+    for B, L, H in _token_shapes():
+        rows, nb, gx, gy, gz = _token(rules, B, L, H)
+        groups = -(-L // 16)
+        assert (gx - 1) * rows < H <= gx * rows, (B, L, H)
+        assert (gz - 1) * nb < B <= gz * nb, (B, L, H)
+        assert 1 <= gy <= min(groups, 1024), (B, L, H)
+        assert gy == groups or gx * gz == 1, (B, L, H)  # a strided walk takes all rows
+        assert gx == 1 or (rows % 4 == 0 and nb == 1), (B, L, H)
+        assert gz <= 65535
+
+
+def test_token_split_repeats_the_angles_only_where_it_pays(rules):
+    """Each share of a token's rows forms the token's angles anew: up to 320
+    groups of tokens (a workgroup per compute unit) a share has at most half the
+    chain of rows, four at a time; past that it has at least eight rows."""
+    for B, L, H in _token_shapes():
+        rows, nb, gx, gy, gz = _token(rules, B, L, H)
+        if gx * gz == 1:
+            continue
+        if -(-L // 16) <= 320:
+            assert 2 * -(-rows * nb // 4) <= -(-B * H // 4) and gx * gy * gz <= 4096, (B, L, H)
+        else:
+            assert rows * nb >= 8 and gx * gy * gz <= 2560, (B, L, H)
+    assert _token(rules, 1, 15600, 5)[2] == 1     # two shares: 10.1 against 8.2 us
+    assert _token(rules, 1, 7800, 12)[2] == 1     # half split, two shares: 13.9 against 11.7 us
+    assert _token(rules, 1, 4680, 10)[2] == 1     # eight heads and two: 7.4 against 6.3 us
+    assert _token(rules, 1, 8200, 40)[2] == 1     # 12, 12, 12 and 4 heads: 30.1 against 27.9 us
+    assert _token(rules, 1, 7800, 40)[2] == 5     # one share: 26.5 against 25.8 us
+    assert _token(rules, 1, 7800, 24)[2] == 2     # one share: 18.6 against 18.0 us
+    assert _token(rules, 1, 1560, 12)[2] == 3     # one share: 8.2 against 6.4 us
