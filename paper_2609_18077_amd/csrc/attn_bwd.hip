@@ -726,11 +726,7 @@ hipError_t launch_attn_bwd(const uint16_t* q, const uint16_t* k, const uint16_t*
   a.B = B; a.H = H; a.Lq = Lq; a.Lk = Lk;
   a.scale = scale;
   a.c = scale * kLog2e;
-  BwdSplit sp = attn_bwd_split(B, H, Lq, Lk, device_cu_count());
-  if (ws_floats < sp.floats) {  // too small a workspace for the split: run unsplit
-    sp.qsplit = 1;
-    sp.qper = (Lq + BN - 1) / BN;
-  }
+  const BwdSplit sp = attn_bwd_split(B, H, Lq, Lk, device_cu_count(), ws_floats);  // what fits the workspace
   a.qsplit = sp.qsplit;
   a.qper = sp.qper;
   a.part = sp.qsplit > 1 ? ws + sp.part_offset : nullptr;

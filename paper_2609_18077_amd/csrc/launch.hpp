@@ -77,28 +77,34 @@ int device_cu_count();
 // units of one tile's (about 3.6 us): rounds x (tiles a run + 2 for a workgroup's
 // start and end), and for a split 3 for the extra launch and the bytes of the
 // fp32 partials (written and read: 16 bytes a gradient value and run, about
-// 14 MB in a tile's time).  The partial dK and dV of the runs follow D in the
-// workspace, from a 256-byte aligned offset; `floats` is the workspace size
-// this needs (B * H * Lq when qsplit is 1).
+// 14 MB in a tile's time); as far as the partials stay within kBwdPartFloats
+// and the whole within max_floats.  192 MiB is what the runs of a launch that
+// fills the chip come to; without that line 3 heads x 39167 took five runs and
+// 601 MB for 6569 us, against 6508 us unsplit.  The partial dK and dV of the runs
+// follow D in the workspace, from a 256-byte aligned offset; `floats` is the
+// workspace size this needs (B * H * Lq when qsplit is 1).
 constexpr int kBwdKeys = 256;
+constexpr size_t kBwdPartFloats = (size_t)48 << 20;
 struct BwdSplit {
   int qsplit, qper;
   size_t part_offset, floats;
 };
 
-inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus) {
+inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus, size_t max_floats) {
   constexpr int kRows = 64;
   BwdSplit r;
   const size_t rows = (size_t)B * H * Lq;
   const int qtiles = (Lq + kRows - 1) / kRows;
   const int64_t nkv = (int64_t)((Lk + kBwdKeys - 1) / kBwdKeys) * B * H;
   r.qsplit = 1;
+  r.part_offset = (rows + 63) / 64 * 64;
   if (nkv > 0 && nkv < 2 * (int64_t)cus && qtiles > 8) {
-    const double part = (double)B * Lk * H * kHeadDim * 16 / 14e6;
+    const size_t run = 2 * (size_t)B * Lk * H * kHeadDim;  // partial values of a run
     double best = 0;
     for (int s = 1; s <= 32 && (s == 1 || s <= qtiles / 2); ++s) {
+      if (s > 1 && (s * run > kBwdPartFloats || r.part_offset + s * run > max_floats)) break;
       const double rounds = (double)((nkv * s + cus - 1) / cus);
-      const double cost = rounds * ((qtiles + s - 1) / s + 2) + (s > 1 ? 3 + s * part : 0);
+      const double cost = rounds * ((qtiles + s - 1) / s + 2) + (s > 1 ? 3 + s * (run * 8 / 14e6) : 0);
       if (s == 1 || cost < best) {
         best = cost;
         r.qsplit = s;
@@ -106,7 +112,6 @@ inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus) {
     }
   }
   r.qper = (qtiles + r.qsplit - 1) / r.qsplit;
-  r.part_offset = (rows + 63) / 64 * 64;
   r.floats = r.qsplit > 1 ? r.part_offset + 2 * (size_t)r.qsplit * B * Lk * H * kHeadDim : rows;
   return r;
 }

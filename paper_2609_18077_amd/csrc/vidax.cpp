@@ -213,7 +213,7 @@ vidax_status vidax_attn_bwd(const void* q, const void* k, const void* v, const v
 size_t vidax_attn_bwd_workspace_floats(int32_t B, int32_t H, int32_t Lq, int32_t Lk, int32_t d) {
   if (B < 0 || H < 0 || Lq < 0 || Lk < 0 || d != vidax::kHeadDim) return 0;
   if (numel4(B, Lq, H, d) < 0 || numel4(B, Lk, H, d) < 0) return 0;
-  return vidax::attn_bwd_split(B, H, Lq, Lk, vidax::device_cu_count()).floats;
+  return vidax::attn_bwd_split(B, H, Lq, Lk, vidax::device_cu_count(), SIZE_MAX).floats;
 }
 
 vidax_status vidax_attn_bwd_noalloc(const void* q, const void* k, const void* v, const void* o, const void* dout,

@@ -238,6 +238,38 @@ def test_attn_bwd_split_matches_unsplit():
         assert bool(((a == 0) == (b == 0)).all()), name
 
 
+@pytest.mark.parametrize("runs", [2, 5])
+def test_attn_bwd_smaller_workspace_takes_fewer_runs(runs):
+    """A workspace below what the full split asks for still splits, into the
+    runs that fit: their partials are written (and nothing past them), and the
+    gradients match the oracle's."""
+    import torch
+
+    w = [c for c in BWD if c.name == "bwd_split"][0]
+    q, k, v, lv = inputs.make_qkv(w)
+    do = inputs.make_dout(w)
+    log(f"case workspace of {runs} runs {w.name}")
+    dec = oracle.bf16_bits_to_f64
+    ob, lse = _oracle_fwd_inputs(dec(q), dec(k), dec(v), w.scale, lv)
+    rows, grad = w.B * w.H * w.Lq, w.B * w.H * w.Lk * w.d
+    first = (rows + 63) // 64 * 64
+    need = first + 2 * runs * grad
+    assert need < vx.lib().vidax_attn_bwd_workspace_floats(w.B, w.H, w.Lq, w.Lk, w.d)
+    ws = torch.full((need + grad,), float("nan"), dtype=torch.float32, device="cuda")
+    dq, dk, dv = vx.attn_bwd(to_dev(q), to_dev(k), to_dev(v), to_dev(ob), to_dev(do), torch.from_numpy(lse).cuda(),
+                             scale=w.scale, kv_valid_len=lengths_dev(lv), workspace=ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(ws[first:need]).all())
+    assert bool(torch.isnan(ws[need:]).all())
+    rq, rk, rv = oracle.attn_bwd_ref(dec(q), dec(k), dec(v), dec(do), w.scale, kv_valid_len=lv, o_saved=dec(ob))
+    dq, dk, dv = to_bits(dq), to_bits(dk), to_bits(dv)
+    kr = _key_rows(lv, w)
+    _check_grad(dv, rv, "dv", kr)
+    _check_grad(dk, rk, "dk", kr)
+    _check_grad(dq, rq, "dq")
+    _check_zeros(dq, dk, dv, lv, w.Lk)
+
+
 def test_attn_bwd_batch_over_2gib():
     """One batch of k, v (and dk, dv) larger than 2 GiB: B=1, H=40, Lk=220000
     keys, 64 queries.  Element (n, h) of k sits at byte (n * 40 + h) * 256,

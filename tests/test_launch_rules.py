@@ -21,6 +21,10 @@ extern "C" void token_rule(int B, int L, int H, int* out) {
   const TokenSplit s = token_split(B, L, H);
   out[0] = s.rows; out[1] = s.nb; out[2] = s.gx; out[3] = s.gy; out[4] = s.gz;
 }
+extern "C" void bwd_rule(int B, int H, int Lq, int Lk, int cus, size_t max_floats, size_t* out) {
+  const BwdSplit s = attn_bwd_split(B, H, Lq, Lk, cus, max_floats);
+  out[0] = s.qsplit; out[1] = s.qper; out[2] = s.part_offset; out[3] = s.floats;
+}
 """
 
 
@@ -85,3 +89,48 @@ def test_token_split_repeats_the_angles_only_where_it_pays(rules):
     assert _token(rules, 1, 7800, 40)[2] == 5     # one share: 26.5 against 25.8 us
     assert _token(rules, 1, 7800, 24)[2] == 2     # one share: 18.6 against 18.0 us
     assert _token(rules, 1, 1560, 12)[2] == 3     # one share: 8.2 against 6.4 us
+
+
+NO_LIMIT = 2 ** 62
+
+
+def _bwd(rules, B, H, Lq, Lk, max_floats=NO_LIMIT, cus=256):
+    out = (ctypes.c_size_t * 4)()
+    rules.bwd_rule(B, H, Lq, Lk, cus, ctypes.c_size_t(max_floats), out)
+    return list(out)
+
+
+def _bwd_shapes():
+    rng = np.random.default_rng(62)
+    return [(int(rng.integers(1, 4)), int(rng.integers(1, 60)), int(np.exp(rng.uniform(0, 11))),
+             int(np.exp(rng.uniform(0, 11)))) for _ in range(300)]
+
+
+def test_bwd_split_fits_its_workspace(rules):
+    """Every query tile lies in one run, the partials end within the workspace
+    the rule asks for and within 192 MiB, and a call with any smaller workspace
+    (down to D alone) takes runs that fit it."""
+    for B, H, Lq, Lk in _bwd_shapes():
+        tiles, rows, run = -(-Lq // 64), B * H * Lq, 2 * B * H * Lk * 128
+        full = _bwd(rules, B, H, Lq, Lk)[3]
+        for limit in (NO_LIMIT, full, full - 1, (full + rows) // 2, rows):
+            if limit < rows:
+                continue
+            qsplit, qper, off, floats = _bwd(rules, B, H, Lq, Lk, limit)
+            assert floats <= limit and floats <= full, (B, H, Lq, Lk, limit)
+            assert 1 <= qsplit <= 32 and qsplit * qper >= tiles
+            if qsplit > 1:
+                assert off % 64 == 0 and off >= rows and floats == off + qsplit * run
+                assert qsplit * run * 4 <= 192 << 20
+            else:
+                assert floats == rows
+
+
+def test_bwd_split_with_a_smaller_workspace_keeps_splitting(rules):
+    """A workspace of the size an earlier choice asked for (fewer runs) is used
+    as far as it goes, not given up for no split at all."""
+    B, H, Lq, Lk = 1, 12, 16384, 77
+    run, rows = 2 * B * H * Lk * 128, B * H * Lq
+    assert _bwd(rules, B, H, Lq, Lk)[0] == 20
+    for s in (2, 8, 16, 19):
+        assert s // 2 < _bwd(rules, B, H, Lq, Lk, rows + 64 + s * run)[0] <= s, s

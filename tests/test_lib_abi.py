@@ -181,13 +181,18 @@ def test_attn_bwd_workspace_floats():
     # many key workgroups, or too few query tiles to cut: D only
     assert f(1, 12, 32760, 32760, 128) == 12 * 32760
     assert f(1, 2, 512, 512, 128) == 2 * 512
-    # text cross-attention shape: 2 x 40 x ceil(512 / 128) = 320 key workgroups
+    # text cross-attention shape: 2 x 40 x ceil(512 / 256) = 160 key workgroups
     # -> cut into runs; D (padded to 64 values) then 2 x qsplit partial tensors
     n = f(2, 40, 32760, 512, 128)
     rows = 2 * 40 * 32760
     grad = 2 * 512 * 40 * 128
     assert n > rows and (n - (rows + 63) // 64 * 64) % (2 * grad) == 0
-    assert 2 <= (n - (rows + 63) // 64 * 64) // (2 * grad) <= 16
+    assert 2 <= (n - (rows + 63) // 64 * 64) // (2 * grad) <= 32
+    # the partials never take more than 192 MiB
+    for B in (1, 2):
+        for H in (1, 3, 5, 10, 24, 40):
+            for Lq, Lk in ((39167, 39167), (131072, 60000), (8000, 8000), (32760, 512), (2600, 20000)):
+                assert f(B, H, Lq, Lk, 128) - B * H * Lq <= (192 << 20) // 4 + 64, (B, H, Lq, Lk)
 
 
 def test_attn_bwd_noalloc_rejects_invalid_arguments():
