@@ -449,47 +449,76 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
   f32x16 dk[4], dv[4];
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) dk[mb] = dv[mb] = f32x16{};
-  // key row `row` (lane holds it), d = 32 mb + 8 g + 4 hi .. + 3: the
-  // accumulators where `row` is a valid key, zero otherwise
-  auto finish = [&](int row) __attribute__((always_inline)) {
+  // With runs: the fp32 partials of key row `row` (lane holds it), d = 32 mb +
+  // 8 g + 4 hi .. + 3: the accumulators where `row` is a valid key, zero otherwise
+  auto partials_out = [&](int row) __attribute__((always_inline)) {
     if (row >= a.Lk) return;
-    const float keep = row < lv ? 1.f : 0.f;
-    const size_t rowoff = ((size_t)b * a.Lk + row) * tok + (size_t)h * D;
-    if (a.qsplit > 1) {
-      const size_t n = (size_t)a.B * a.Lk * tok;
-      float* pk = a.part + (size_t)sp * n + rowoff;
-      float* pv = a.part + (size_t)(a.qsplit + sp) * n + rowoff;
+    const size_t rowoff = ((size_t)b * a.Lk + row) * tok + (size_t)h * D, n = (size_t)a.B * a.Lk * tok;
+    float* pk = a.part + (size_t)sp * n + rowoff;
+    float* pv = a.part + (size_t)(a.qsplit + sp) * n + rowoff;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-          if (keep != 0.f) {
-            x = make_float4(dk[mb][4 * g], dk[mb][4 * g + 1], dk[mb][4 * g + 2], dk[mb][4 * g + 3]);
-            y = make_float4(dv[mb][4 * g], dv[mb][4 * g + 1], dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
-          }
-          *reinterpret_cast<float4*>(pk + 32 * mb + 8 * g + 4 * hi) = x;
-          *reinterpret_cast<float4*>(pv + 32 * mb + 8 * g + 4 * hi) = y;
+      for (int g = 0; g < 4; ++g) {
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+        if (row < lv) {
+          x = make_float4(dk[mb][4 * g], dk[mb][4 * g + 1], dk[mb][4 * g + 2], dk[mb][4 * g + 3]);
+          y = make_float4(dv[mb][4 * g], dv[mb][4 * g + 1], dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
         }
-    } else {
+        *reinterpret_cast<float4*>(pk + 32 * mb + 8 * g + 4 * hi) = x;
+        *reinterpret_cast<float4*>(pv + 32 * mb + 8 * g + 4 * hi) = y;
+      }
+  };
+  // Otherwise the gradient rows leave whole (16 lanes a 256-byte row), through
+  // an LDS area of the wave's own: stored from the accumulators, 8 bytes of 64
+  // rows an instruction, they made short query streams 5 to 30 % slower (64
+  // queries x 300 keys x 130 heads, whole backward: 45.4 -> 33.6 us).
+  // buffer over 32 key rows from `row` on (none past Lk) of dk or dv, and what the lane
+  // moves of rows 4 i .. 4 i + 3 (position lane & 15 of row 4 i + (lane >> 4))
+  auto rows_rsrc = [&](uint16_t* base, int row) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(base + ((size_t)b * a.Lk + row) * tok + (size_t)h * D), (short)0,
+        __builtin_amdgcn_readfirstlane(min(max(a.Lk - row, 0), 32) * rbytes), kBufferFlags);
+  };
+  auto row_off = [&](int i) __attribute__((always_inline)) {
+    const int r = 4 * i + (lane >> 4);
+    return r * rbytes + ((lane & 15) ^ swz(r)) * 16;
+  };
+  // zeros to the 32 rows from `row` on
+  auto zero_rows = [&](int row) __attribute__((always_inline)) {
+    if (a.qsplit > 1) return partials_out(row + l32);
+    const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 x = make_uint2(0u, 0u), y = x;
-          if (keep != 0.f) {
-            x.x = pack_bf16x2(dk[mb][4 * g] * a.scale, dk[mb][4 * g + 1] * a.scale);
-            x.y = pack_bf16x2(dk[mb][4 * g + 2] * a.scale, dk[mb][4 * g + 3] * a.scale);
-            y.x = pack_bf16x2(dv[mb][4 * g], dv[mb][4 * g + 1]);
-            y.y = pack_bf16x2(dv[mb][4 * g + 2], dv[mb][4 * g + 3]);
-          }
-          *reinterpret_cast<uint2*>(a.dk + rowoff + 32 * mb + 8 * g + 4 * hi) = x;
-          *reinterpret_cast<uint2*>(a.dv + rowoff + 32 * mb + 8 * g + 4 * hi) = y;
-        }
+    for (int i = 0; i < 8; ++i) {
+      __builtin_amdgcn_raw_buffer_store_b128(z, rows_rsrc(a.dk, row), row_off(i), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(z, rows_rsrc(a.dv, row), row_off(i), 0, 0);
     }
   };
+  // acc * mul (zero past the valid keys) to the 32 rows from `row` on, whole rows, through area
+  auto rows_out = [&](uint16_t* dst, int row, const f32x16 acc[4], float mul, uint16_t* area) __attribute__((always_inline)) {
+    const bool keep = row + l32 < lv;
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        uint2 pk = make_uint2(0u, 0u);
+        if (keep) {
+          pk.x = pack_bf16x2(acc[mb][4 * g + 0] * mul, acc[mb][4 * g + 1] * mul);
+          pk.y = pack_bf16x2(acc[mb][4 * g + 2] * mul, acc[mb][4 * g + 3] * mul);
+        }
+        *reinterpret_cast<uint2*>(area + l32 * D + ((4 * mb + g) ^ swz(l32)) * 8 + 4 * hi) = pk;
+      }
+    wave_lds_fence();
+    const __amdgpu_buffer_rsrc_t rs = rows_rsrc(dst, row);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const u32x4 x = *reinterpret_cast<const u32x4*>(area + (4 * i + (lane >> 4)) * D + (lane & 15) * 8);
+      __builtin_amdgcn_raw_buffer_store_b128(x, rs, row_off(i), 0, 0);
+    }
+    wave_lds_fence();
+  };
   if (nvalid <= 0 || t0 >= t1) {  // no valid key (zero gradient) or no query in this run
-    if (wave * 32 < a.kper) finish(key0 + wave * 32 + l32);
+    if (wave * 32 < a.kper) zero_rows(key0 + wave * 32);
     return;
   }
   const bool paired = nvalid <= BK / 2 || a.kper < BK;  // uniform: two waves per 32-key group
@@ -657,7 +686,7 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
     }
     __syncthreads();
     if (part == 1) {
-      if (a.kper == BK) finish(krow + BK / 2);  // the upper half of the tile holds no valid key: zero
+      if (a.kper == BK) zero_rows(key0 + kg * 32 + BK / 2);  // the upper half of the tile holds no valid key: zero
       return;
     }
 #pragma unroll
@@ -670,7 +699,10 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
         dv[mb][4 * g] += y.x; dv[mb][4 * g + 1] += y.y; dv[mb][4 * g + 2] += y.z; dv[mb][4 * g + 3] += y.w;
       }
   }
-  finish(krow);
+  if (a.qsplit > 1) return partials_out(krow);
+  uint16_t* const area = KB + (paired ? 2 : 1) * kg * KOWN;  // read by this wave alone
+  rows_out(a.dk, key0 + kg * 32, dk, a.scale, area);
+  rows_out(a.dv, key0 + kg * 32, dv, 1.f, area);
 }
 
 // ---- dK = scale * sum of the partials, dV = sum of the partials (qsplit >
@@ -726,11 +758,11 @@ hipError_t launch_attn_bwd(const uint16_t* q, const uint16_t* k, const uint16_t*
   a.B = B; a.H = H; a.Lq = Lq; a.Lk = Lk;
   a.scale = scale;
   a.c = scale * kLog2e;
-  const BwdSplit sp = attn_bwd_split(B, H, Lq, Lk, device_cu_count(), ws_floats);  // what fits the workspace
+  const BwdSplit sp = attn_bwd_split(B, H, Lq, Lk, device_cu_count(), ws_floats, kv_valid_len != nullptr);
   a.qsplit = sp.qsplit;
   a.qper = sp.qper;
   a.part = sp.qsplit > 1 ? ws + sp.part_offset : nullptr;
-  a.kper = BK;
+  a.kper = sp.kper;
   hipError_t e = hipSuccess;
   if (Lq > 0) {
     const bool short_keys = (Lk + BN - 1) / BN <= kDqShortTiles;
@@ -742,8 +774,6 @@ hipError_t launch_attn_bwd(const uint16_t* q, const uint16_t* k, const uint16_t*
     if (e != hipSuccess) return e;
   }
   if (Lk > 0) {
-    const bool few = a.qsplit == 1 && (int64_t)((Lk + BK / 2 - 1) / (BK / 2)) * B * H <= device_cu_count();
-    a.kper = few ? BK / 2 : BK;
     a.ntile = (Lk + a.kper - 1) / a.kper;
     a.nwg = a.ntile * B * H * a.qsplit;
     e = launch_kernel(bwd_dkdv_kernel, (unsigned)a.nwg, (unsigned)NT, stream, a);

@@ -99,6 +99,14 @@ __device__ __forceinline__ void for_slots(F&& f) {
   for_slots_of<N>(f, std::make_integer_sequence<int, N>());
 }
 
+// Between LDS writes of a wave's lanes and reads of them by its other lanes (or
+// the reverse): the compiler moves no LDS access across.  No instruction: a
+// wave's LDS accesses are carried out in order.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // End of a slot of a hand-scheduled block: no instruction moves across it.
 #define SLOT() __builtin_amdgcn_sched_barrier(0)
 

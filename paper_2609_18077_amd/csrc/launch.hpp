@@ -68,45 +68,59 @@ hipError_t launch_rope3d(const uint16_t* x, uint16_t* y, int B, int L, int H, co
 // Compute units of the current device (queried once per device).
 int device_cu_count();
 
-// Query-stream split of the backward's key-side kernel.  Its workgroups own
-// kBwdKeys keys of one (b, h), one workgroup per compute unit, and stream
-// every query in 64-row tiles; where there are fewer of them than twice the
-// compute units and more than 8 query tiles, the tiles may be cut into qsplit
-// runs of qper tiles (at least 2 tiles a run, at most 32 runs; up to 8
-// tiles, 128-key workgroups without a split were faster by 3 to 22%).  Chosen: the least time in
-// units of one tile's (about 3.6 us): rounds x (tiles a run + 2 for a workgroup's
-// start and end), and for a split 3 for the extra launch and the bytes of the
-// fp32 partials (written and read: 16 bytes a gradient value and run, about
-// 14 MB in a tile's time); as far as the partials stay within kBwdPartFloats
-// and the whole within max_floats.  192 MiB is what the runs of a launch that
-// fills the chip come to; without that line 3 heads x 39167 took five runs and
-// 601 MB for 6569 us, against 6508 us unsplit.  The partial dK and dV of the runs
-// follow D in the workspace, from a 256-byte aligned offset; `floats` is the
-// workspace size this needs (B * H * Lq when qsplit is 1).
+// Shape of the backward's key-side launch: workgroups of kper = kBwdKeys keys
+// of one (b, h), or of half as many (two waves a 32-key group), one workgroup
+// per compute unit, that stream the queries in 64-row tiles; with full
+// workgroups the tiles may be cut into qsplit runs of qper tiles (at least 2
+// tiles a run, at most 32 runs), whose fp32 partial dK and dV a further launch
+// adds up.  Chosen is the least time in units of one tile's:
+//   unsplit   rounds x (tiles + 2.6), half workgroups rounds x (0.55 tiles +
+//             2.8), fitted to 150 shapes of 64 to 500 queries x 256 to 640 keys
+//             x 70 to 400 heads.  300 x 300: 130 heads, 2 rounds of either,
+//             61.8 (full) and 53.6 us; 200 heads, 2 and 3 rounds, 73.0 and
+//             75.8.  Where batches have lengths of their own, half workgroups
+//             only if that takes no more rounds: the full ones past a batch's
+//             end cost nothing (2 x 12 heads x 3000, lengths 1000 and 3000:
+//             2 and 3 rounds, 285 and 303 us);
+//   runs      rounds x (tiles a run + 2) + 3 for the extra launch + the bytes
+//             of the partials, written and read: 16 bytes a gradient value and
+//             run, 14 MB in a tile's time.
+// Runs are considered where full workgroups number less than twice the compute
+// units and there are more than 8 query tiles (up to 8, unsplit was faster by
+// 3 to 22 %), as far as the partials stay within kBwdPartFloats and the whole
+// within max_floats.  192 MiB is what the runs of a launch that fills the chip
+// come to; without that line 3 heads x 39167 took five runs and 601 MB for 6569
+// us, against 6508 us unsplit.  The partials follow D in the workspace, from a
+// 256-byte aligned offset; `floats` is the workspace the choice needs (B * H * Lq
+// when qsplit is 1).
 constexpr int kBwdKeys = 256;
 constexpr size_t kBwdPartFloats = (size_t)48 << 20;
 struct BwdSplit {
-  int qsplit, qper;
+  int kper, qsplit, qper;
   size_t part_offset, floats;
 };
 
-inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus, size_t max_floats) {
+inline BwdSplit attn_bwd_split(int B, int H, int Lq, int Lk, int cus, size_t max_floats, bool lengths) {
   constexpr int kRows = 64;
   BwdSplit r;
   const size_t rows = (size_t)B * H * Lq;
   const int qtiles = (Lq + kRows - 1) / kRows;
-  const int64_t nkv = (int64_t)((Lk + kBwdKeys - 1) / kBwdKeys) * B * H;
+  auto workgroups = [&](int keys) { return (int64_t)((Lk + keys - 1) / keys) * B * H; };
+  auto rounds = [&](int64_t wgs) { return (wgs + cus - 1) / cus; };
+  const int64_t nkv = workgroups(kBwdKeys), r_full = rounds(nkv), r_half = rounds(workgroups(kBwdKeys / 2));
+  const double full = r_full * (qtiles + 2.6), half = r_half * (0.55 * qtiles + 2.8);
+  r.kper = half < full && (!lengths || r_half <= r_full) ? kBwdKeys / 2 : kBwdKeys;
   r.qsplit = 1;
   r.part_offset = (rows + 63) / 64 * 64;
   if (nkv > 0 && nkv < 2 * (int64_t)cus && qtiles > 8) {
     const size_t run = 2 * (size_t)B * Lk * H * kHeadDim;  // partial values of a run
-    double best = 0;
-    for (int s = 1; s <= 32 && (s == 1 || s <= qtiles / 2); ++s) {
-      if (s > 1 && (s * run > kBwdPartFloats || r.part_offset + s * run > max_floats)) break;
-      const double rounds = (double)((nkv * s + cus - 1) / cus);
-      const double cost = rounds * ((qtiles + s - 1) / s + 2) + (s > 1 ? 3 + s * (run * 8 / 14e6) : 0);
-      if (s == 1 || cost < best) {
+    double best = half < full ? half : full;
+    for (int s = 2; s <= 32 && s <= qtiles / 2; ++s) {
+      if (s * run > kBwdPartFloats || r.part_offset + s * run > max_floats) break;
+      const double cost = rounds(nkv * s) * ((qtiles + s - 1) / s + 2) + 3 + s * (run * 8 / 14e6);
+      if (cost < best) {
         best = cost;
+        r.kper = kBwdKeys;
         r.qsplit = s;
       }
     }

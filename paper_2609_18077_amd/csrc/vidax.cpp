@@ -181,7 +181,8 @@ vidax_status bwd_common(bool noalloc, const void* q, const void* k, const void* 
     for (int j = i + 1; j < 4; ++j)
       if (overlaps(outs[i], osz[i], outs[j], osz[j])) return VIDAX_ERR_INVALID_ARG;
   }
-  // grids: dq up to ceil(Lq / 128) B H, key side ceil(Lk / 256) B H (a split has at most 64 workgroups per CU)
+  // grids: dq at most ceil(Lq / 128) B H, key side ceil(Lk / 128) B H or 64 per CU
+  // (its bound is a wide one, kept so that the same calls are refused)
   const int64_t grid_q = ((int64_t)Lq + 127) / 128 * B * H, grid_k = ((int64_t)Lk + 127) / 128 * 16 * B * H;
   if (grid_q > INT32_MAX || grid_k > INT32_MAX) return VIDAX_ERR_UNSUPPORTED;
   // buffer offsets are 32-bit and relative to a 64-row tile
@@ -213,7 +214,7 @@ vidax_status vidax_attn_bwd(const void* q, const void* k, const void* v, const v
 size_t vidax_attn_bwd_workspace_floats(int32_t B, int32_t H, int32_t Lq, int32_t Lk, int32_t d) {
   if (B < 0 || H < 0 || Lq < 0 || Lk < 0 || d != vidax::kHeadDim) return 0;
   if (numel4(B, Lq, H, d) < 0 || numel4(B, Lk, H, d) < 0) return 0;
-  return vidax::attn_bwd_split(B, H, Lq, Lk, vidax::device_cu_count(), SIZE_MAX).floats;
+  return vidax::attn_bwd_split(B, H, Lq, Lk, vidax::device_cu_count(), SIZE_MAX, false).floats;
 }
 
 vidax_status vidax_attn_bwd_noalloc(const void* q, const void* k, const void* v, const void* o, const void* dout,

@@ -116,10 +116,12 @@ BWD = [
     inputs.custom("bwd_one", B=2, H=1, Lq=1, Lk=1, seed=35),
     inputs.custom("bwd_edges", B=1, H=2, Lq=257, Lk=65, seed=36),
     inputs.custom("bwd_normed", B=1, H=2, Lq=1536, Lk=1536, seed=37, rms_norm_qk=True),
-    # few key workgroups and a long query stream: the key-side kernels cut the
-    # 127 query tiles into 15 runs of 9 (fp32 partials summed afterwards), the
-    # last run one tile; a batch with few valid keys
+    # few key workgroups and a long query stream: the key-side kernel cuts the
+    # 127 query tiles into 16 runs of 8, the last of 7 (fp32 partials summed
+    # afterwards); a batch with few valid keys
     inputs.custom("bwd_split", B=2, H=4, Lq=8100, Lk=300, seed=38, kv_valid=("fixed", [300, 45])),
+    # 41 query tiles in 11 runs of 4, the last of one
+    inputs.custom("bwd_split_tail", B=1, H=4, Lq=2600, Lk=700, seed=41, kv_valid=("fixed", [641])),
 ]
 
 
@@ -128,16 +130,24 @@ def test_attn_bwd_matches_oracle(w):
     _bwd_case(w)
 
 
-@pytest.mark.parametrize("Lq,Lk,lens", [
-    (200, 512, [1, 32, 33]),       # at most 128 valid keys: two waves a 32-key group
-    (321, 300, [127, 128, 129]),   # the edge between the two forms
-    (64, 513, [256, 257, 513]),    # one query tile; the edge of a 256-key workgroup
-    (130, 256, [97, 255, 300]),    # split into one-tile runs where it splits
+@pytest.mark.parametrize("H,Lq,Lk,lens", [
+    # few heads: 128 keys a workgroup, two waves a 32-key group
+    (2, 200, 512, [1, 32, 33]),
+    (2, 321, 300, [127, 128, 129]),
+    (2, 64, 513, [256, 257, 513]),    # one query tile
+    (2, 130, 256, [97, 255, 300]),
+    # 129 heads: 256 keys a workgroup; up to 128 valid ones of them are given to
+    # two waves a group, more to one
+    (43, 200, 512, [1, 33, 128]),
+    (43, 130, 512, [127, 128, 129]),
+    (43, 64, 513, [256, 257, 513]),
+    (43, 130, 512, [97, 225, 511]),
 ], ids=str)
-def test_attn_bwd_key_groups(Lq, Lk, lens):
+def test_attn_bwd_key_groups(H, Lq, Lk, lens):
     """Valid lengths at the edges of the key-side kernel's 32-key groups, of
-    its two forms (up to and past 128 valid keys) and of its 256-key tiles."""
-    _bwd_case(inputs.custom("bwd_keys", B=3, H=2, Lq=Lq, Lk=Lk, seed=39, kv_valid=("fixed", lens)))
+    its two forms (up to and past 128 valid keys) and of its 128- and 256-key
+    tiles."""
+    _bwd_case(inputs.custom("bwd_keys", B=3, H=H, Lq=Lq, Lk=Lk, seed=39, kv_valid=("fixed", lens)))
 
 
 @pytest.mark.parametrize("H,Lq,Lk,lens", [

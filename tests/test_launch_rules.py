@@ -21,9 +21,9 @@ extern "C" void token_rule(int B, int L, int H, int* out) {
   const TokenSplit s = token_split(B, L, H);
   out[0] = s.rows; out[1] = s.nb; out[2] = s.gx; out[3] = s.gy; out[4] = s.gz;
 }
-extern "C" void bwd_rule(int B, int H, int Lq, int Lk, int cus, size_t max_floats, size_t* out) {
-  const BwdSplit s = attn_bwd_split(B, H, Lq, Lk, cus, max_floats);
-  out[0] = s.qsplit; out[1] = s.qper; out[2] = s.part_offset; out[3] = s.floats;
+extern "C" void bwd_rule(int B, int H, int Lq, int Lk, int cus, size_t max_floats, int lengths, size_t* out) {
+  const BwdSplit s = attn_bwd_split(B, H, Lq, Lk, cus, max_floats, lengths != 0);
+  out[0] = s.kper; out[1] = s.qsplit; out[2] = s.qper; out[3] = s.part_offset; out[4] = s.floats;
 }
 """
 
@@ -94,9 +94,9 @@ def test_token_split_repeats_the_angles_only_where_it_pays(rules):
 NO_LIMIT = 2 ** 62
 
 
-def _bwd(rules, B, H, Lq, Lk, max_floats=NO_LIMIT, cus=256):
-    out = (ctypes.c_size_t * 4)()
-    rules.bwd_rule(B, H, Lq, Lk, cus, ctypes.c_size_t(max_floats), out)
+def _bwd(rules, B, H, Lq, Lk, max_floats=NO_LIMIT, lengths=False, cus=256):
+    out = (ctypes.c_size_t * 5)()
+    rules.bwd_rule(B, H, Lq, Lk, cus, ctypes.c_size_t(max_floats), int(lengths), out)
     return list(out)
 
 
@@ -112,18 +112,20 @@ def test_bwd_split_fits_its_workspace(rules):
     (down to D alone) takes runs that fit it."""
     for B, H, Lq, Lk in _bwd_shapes():
         tiles, rows, run = -(-Lq // 64), B * H * Lq, 2 * B * H * Lk * 128
-        full = _bwd(rules, B, H, Lq, Lk)[3]
+        full = _bwd(rules, B, H, Lq, Lk)[4]
         for limit in (NO_LIMIT, full, full - 1, (full + rows) // 2, rows):
             if limit < rows:
                 continue
-            qsplit, qper, off, floats = _bwd(rules, B, H, Lq, Lk, limit)
-            assert floats <= limit and floats <= full, (B, H, Lq, Lk, limit)
-            assert 1 <= qsplit <= 32 and qsplit * qper >= tiles
-            if qsplit > 1:
-                assert off % 64 == 0 and off >= rows and floats == off + qsplit * run
-                assert qsplit * run * 4 <= 192 << 20
-            else:
-                assert floats == rows
+            for lengths in (False, True):
+                kper, qsplit, qper, off, floats = _bwd(rules, B, H, Lq, Lk, limit, lengths)
+                assert floats <= limit and floats <= full, (B, H, Lq, Lk, limit)
+                assert 1 <= qsplit <= 32 and qsplit * qper >= tiles
+                assert kper in (128, 256) and (qsplit == 1 or kper == 256)
+                if qsplit > 1:
+                    assert off % 64 == 0 and off >= rows and floats == off + qsplit * run
+                    assert qsplit * run * 4 <= 192 << 20
+                else:
+                    assert floats == rows
 
 
 def test_bwd_split_with_a_smaller_workspace_keeps_splitting(rules):
@@ -131,6 +133,21 @@ def test_bwd_split_with_a_smaller_workspace_keeps_splitting(rules):
     as far as it goes, not given up for no split at all."""
     B, H, Lq, Lk = 1, 12, 16384, 77
     run, rows = 2 * B * H * Lk * 128, B * H * Lq
-    assert _bwd(rules, B, H, Lq, Lk)[0] == 20
+    assert _bwd(rules, B, H, Lq, Lk)[1] == 20
     for s in (2, 8, 16, 19):
-        assert s // 2 < _bwd(rules, B, H, Lq, Lk, rows + 64 + s * run)[0] <= s, s
+        assert s // 2 < _bwd(rules, B, H, Lq, Lk, rows + 64 + s * run)[1] <= s, s
+
+
+def test_bwd_key_workgroups(rules):
+    """128 or 256 keys a workgroup, on the measured sides of the line."""
+    full, half = 256, 128
+    assert _bwd(rules, 1, 130, 300, 300)[0] == half   # 2 rounds of either: 61.8 against 53.6 us
+    assert _bwd(rules, 1, 100, 300, 600)[0] == half   # 73.2 against 68.9 us
+    assert _bwd(rules, 1, 200, 300, 300)[0] == full   # 2 against 3 rounds: 73.0 and 75.8 us
+    assert _bwd(rules, 1, 200, 500, 512)[0] == full   # 2 against 4 rounds: 112.6 and 134.3 us
+    assert _bwd(rules, 1, 260, 64, 300)[0] == full    # 3 against 4 rounds of one tile: 53.7 and 55.1 us
+    assert _bwd(rules, 1, 260, 500, 300)[0] == half   # of eight tiles: 140.6 and 130.9 us
+    assert _bwd(rules, 1, 12, 1560, 1560)[:2] == [half, 1]  # runs: 103.8 against 93.9 us
+    # lengths of their own: no more rounds than with full workgroups
+    assert _bwd(rules, 2, 12, 3000, 3000)[0] == half
+    assert _bwd(rules, 2, 12, 3000, 3000, lengths=True)[0] == full
