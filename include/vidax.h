@@ -153,6 +153,11 @@ vidax_status vidax_qk_norm_rope(const void* x, void* y, const float* gain, float
  *   One batch of a tensor, max(Lq, Lk) * H * d * 2 bytes, must stay below
  *   2 GiB - 4 KiB (the kernels use 32-bit buffer offsets within a batch):
  *   VIDAX_ERR_UNSUPPORTED beyond; vidax_attn_fwd_naive has the same limit.
+ *   One of three kernels runs, by the sizes of the call and the device's
+ *   compute units.  Calls of the same sizes give the same bits; the same head
+ *   in calls of other sizes (a tensor-parallel shard against all heads) may
+ *   differ by the roundings of the softmax weights to bf16, 2.5e-3 of the
+ *   output's norm, with the same error against exact arithmetic.
  */
 vidax_status vidax_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                             int32_t B, int32_t H, int32_t Lq, int32_t Lk, int32_t d, float scale,

@@ -517,8 +517,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(AttnArgs a) {
 
   // ---- output: O = O^T / l (zero when no key is valid), LSE = m + ln l,
   // through the staging area.  Buffer stores: rows past Lq address past the
-  // records and are dropped, so every wave issues exactly kOutStores store
-  // instructions.
+  // records and are dropped.
   auto store_o = [&](int ob, int oh, int orow, bool olive, bool empty) __attribute__((always_inline)) {
     const float l = wave_half_sum(lsum);
     const float inv = empty ? 0.f : 1.0f / l;
@@ -580,12 +579,18 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(AttnArgs a) {
 }
 
 // The 128-row kernel with two key groups (attn_fwd_split.hip) runs where its
-// workgroups still fit the compute units in one round, i.e. where this kernel
-// would leave at least half of them idle, and where there are enough key steps
-// to repay the merge.  Measured (rotated queries, this kernel -> that one): 84
-// tiles of 256 rows, 1560 keys 42.5 -> 37.8 us, 75 tiles, 3600 keys 82 -> 66,
-// 124 tiles, 7800 keys 160 -> 137; 180 tiles (156 .. 256 would be two rounds)
-// 90 -> 138; 6 tiles, 345 keys 17.7 -> 18.1, 4 tiles, 512 keys 19.5 -> 19.2.
+// workgroups fit the compute units in one round and there are enough key steps
+// to repay the merge.  It shortens a workgroup's chain, also where this kernel
+// has as many workgroups (at most 128 query rows).  Measured (this kernel ->
+// that one, us):                  unrotated     rotated queries  keys too
+//   2 heads x 512 x 512           16.3 -> 14.6  19.5 -> 17.6     24.7 -> 19.5
+//   64 x 512 x 512 (256 tiles)    17.4 -> 16.0  20.7 -> 18.9     26.5 -> 21.2
+//   256 x 128 x 512 (the same)    19.9 -> 19.1  22.6 -> 21.8     28.4 -> 22.1
+//   12 x 1560 x 1560 (156)        38.8 -> 31.3  42.2 -> 35.0     59.9 -> 44.3
+//   8 x 4000 x 4000 (256)         85.5 -> 69.0  86.5 -> 72.0    125.6 -> 89.0
+// Two rounds are slower (180 tiles of 256 rows, 90 -> 138).  With few valid keys
+// of many it gains nothing: 64 of 4096, 7.4 -> 7.9, 11.3 -> 11.5, 11.8 -> 12.0;
+// from 200 on it does.
 constexpr int kSplitMinKeys = 512;
 bool use_split(int Lq, int B, int H, int Lk, int cus) {
   return Lk >= kSplitMinKeys && (int64_t)((Lq + kSplitRows - 1) / kSplitRows) * B * H <= cus;

@@ -10,9 +10,12 @@
 // per wave.  K and V have four tile buffers, so that a copy has three steps to
 // land (the dense kernel's two give it one, enough where every compute unit is
 // at work and a step is longer than a copy's latency).
-// At 12 heads x 1560 x 1560 (rotated queries): 42.5 -> 37.8 us; 5 heads x 3600 x
-// 3600: 82 -> 66; keys rotated here too, 1560 x 12: 60 -> 53 (see the rule at
-// use_split).
+// No instance spills: a spilled register's store or reload waits behind the copies
+// just issued, at the start and end of a chain that is little else (54, 35 and 17
+// spilled registers cost 13, 10 and 5 % at 12 x 512).
+// At 12 heads x 1560 x 1560 (rotated queries): 42.2 -> 35.0 us; 8 heads x 4000 x
+// 4000: 86.5 -> 72.0; keys rotated here too, 59.9 -> 44.3 and 125.6 -> 89.0 (see
+// the rule at use_split).
 //
 // LDS: K and V tiles 8 x 16 KB (rotating keys: 4), rotary table <= 32 KB; query
 // and output staging in the K and V buffers.
@@ -271,17 +274,11 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
   const int koff = grp * TILE + lane * 8;
   const int voff = grp * TILE + lane * 4;
 
-  // Rotated query (scaled into log2 units): the score accumulators start at
-  // -cbase instead of zero, so that the products come out as s - cbase with
-  // no vector work.  Unrotated query: they start at zero and p = exp2(s c2 -
-  // mref) takes one FMA (cbase stays 0).
   float mref = -INFINITY;  // reference max (log2 units), identical in both lane halves
-  float cbase = 0.f;       // the offset the score accumulators start from (mref once finite)
-  f32x16 cneg = f32x16{};
   auto qk = [&](const uint16_t* kb, f32x16& s) __attribute__((always_inline)) {
 #pragma unroll
     for (int st = 0; st < 8; ++st)
-      s = mfma32(*reinterpret_cast<const bf16x8*>(kb + st * BLK + koff), qreg[st], st == 0 ? (ROPE ? cneg : f32x16{}) : s);
+      s = mfma32(*reinterpret_cast<const bf16x8*>(kb + st * BLK + koff), qreg[st], st == 0 ? f32x16{} : s);
   };
 
   f32x16 oacc[4];
@@ -290,10 +287,12 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) oacc[mb] = f32x16{};
 
-  const float c2 = a.c2;
-  // p = exp2(s) (rotated query: scores already relative to the reference) or
-  // exp2(s c2 - mref) for the 32 keys of one key block as two bf16 MFMA
-  // operands (16 keys each); returns tsum plus this lane's sum of p
+  // p = exp2(s c2 - mref) for the 32 keys of one key block as two bf16 MFMA
+  // operands (16 keys each); returns tsum plus this lane's sum of p.  A rotated
+  // query is scaled into log2 units (c2 = 1).  (The dense kernel starts the
+  // score accumulators of rotated queries at -mref instead; here the 16
+  // registers of that start are what would spill.)
+  const float c2 = ROPE ? 1.f : a.c2;
   auto softmax_p = [&](const f32x16& s, bf16x8 pop[2], float tsum) __attribute__((always_inline)) {
     const float nm = -mref;
 #pragma unroll
@@ -301,8 +300,8 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
       uint32_t pw[4];
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(ROPE ? s[8 * ks + e] : fmaf(s[8 * ks + e], c2, nm));
-        const float p1 = __builtin_amdgcn_exp2f(ROPE ? s[8 * ks + e + 1] : fmaf(s[8 * ks + e + 1], c2, nm));
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[8 * ks + e], c2, nm));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[8 * ks + e + 1], c2, nm));
         pw[e >> 1] = pack_bf16x2(p0, p1);
         tsum = dot2(pw[e >> 1], kOnesBf16x2, tsum);
       }
@@ -313,33 +312,21 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
 
   // Probabilities of one key block.  The first block (its sum starts at
   // +inf) and a block whose row sum of p leaves [0, 2^64) reset the
-  // reference to the running max, rescaling the output (which may already
-  // hold the other block of the same tile) and the sum (see the header).
-  // Score blocks already computed from the old offset are shifted to the new
-  // one (shift_pending(delta)).
-  auto softmax_blk = [&](f32x16& s, bf16x8 pop[2], auto&& shift_pending) __attribute__((always_inline)) {
+  // reference to the running max, rescaling the output and the sum.
+  auto softmax_blk = [&](const f32x16& s, bf16x8 pop[2]) __attribute__((always_inline)) {
     float tsum = softmax_p(s, pop, sum0);
     if (__builtin_amdgcn_ballot_w64(!(tsum < kSumLimit)) != 0) {
       sum0 = 0.f;
       float m = fmaxf(s[0], s[1]);
 #pragma unroll
       for (int i = 2; i < 16; ++i) m = fmaxf(m, s[i]);
-      const float mnew = fmaxf(mref, ROPE ? wave_half_max(m) + cbase : wave_half_max(m) * c2);
+      const float mnew = fmaxf(mref, wave_half_max(m) * c2);
       const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
       lsum *= alpha;
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
-      if (ROPE) {
-        const float delta = mnew - cbase;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] -= delta;
-        shift_pending(delta);
-        cbase = mnew;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cneg[i] = -mnew;
-      }
       mref = mnew;
       tsum = softmax_p(s, pop, 0.f);
     }
@@ -359,15 +346,9 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
       }
     }
   };
-  // softmax and PV of one score tile (snext: the next tile's scores, already
-  // computed from the old offset, or null)
-  auto softmax_pv = [&](f32x16& s, const uint16_t* vb, f32x16* snext) __attribute__((always_inline)) {
+  auto softmax_pv = [&](const f32x16& s, const uint16_t* vb) __attribute__((always_inline)) {
     bf16x8 pop[2];
-    softmax_blk(s, pop, [&](float delta) __attribute__((always_inline)) {
-      if (snext)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) (*snext)[i] -= delta;
-    });
+    softmax_blk(s, pop);
     pv(vb, pop);
   };
 
@@ -415,28 +396,33 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
   // Step j (R = j mod NBUF): scores of tile j + 1, softmax and PV of tile j,
   // while K_{j+NBUF} and V_{j+NBUF-1} stream into the buffers that tiles j and
   // j - 1 have freed.  The buffers are chosen at compile time.
-  auto step = [&](auto phase, int j, f32x16& scur, f32x16& snext) __attribute__((always_inline)) {
+  // LAST (rotated keys): the last tile but one, no K tile to rotate behind it.
+  auto step_of = [&](auto phase, auto last, int j, f32x16& scur, f32x16& snext) __attribute__((always_inline)) {
     constexpr int R = decltype(phase)::value;
+    constexpr bool LOAD_K = ROPE_K && !decltype(last)::value;
     uint16_t* const kfree = kbuf(R);               // held K_j
     uint16_t* const knext = kbuf(R + 1);           // holds K_{j+1}
     uint16_t* const vcur = vbuf(R);                // holds V_j
     uint16_t* const vfree = vbuf(R + NBUF - 1);    // held V_{j-1}
     uint4 kn[2];
     float2 cs[2][4];
-    if (ROPE_K) {
+    if (LOAD_K) {
       load_k(j + 2, kn);
       fetch_coef(j + 2, cs);
-    } else {
+    } else if (!ROPE_K) {
       dma_tile(kbh, j + NBUF, kfree, kg0, kg1);
     }
     dma_tile(vbh, j + NBUF - 1, vfree, vg0, vg1);
     if (live) {
       qk(knext, snext);
-      softmax_pv(scur, vcur, &snext);
+      softmax_pv(scur, vcur);
     }
-    if (ROPE_K) store_k(kfree, kn, cs);
+    if (LOAD_K) store_k(kfree, kn, cs);
     copies_landed();
     step_barrier();
+  };
+  auto step = [&](auto phase, int j, f32x16& scur, f32x16& snext) __attribute__((always_inline)) {
+    step_of(phase, std::false_type(), j, scur, snext);
   };
 
   // the tile whose first copies have landed (and been published): scores of
@@ -472,12 +458,12 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + 4 * hi + (i & 3) >= rem) s[i] = -INFINITY;
       }
-      softmax_pv(s, vb, nullptr);
+      softmax_pv(s, vb);
     };
     // (a copy of the end for each place where the steps can stop: a choice of
     // the score registers at run time would put them into memory)
     if (j + 1 >= nsteps) return finish(sa, vbuf(0));
-    step(r0(), j, sa, sb);
+    step_of(r0(), std::integral_constant<bool, ROPE_K>(), j, sa, sb);
     if (NBUF == 2 || j + 2 >= nsteps) {
       ++j;
       return finish(sb, vbuf(1));
@@ -492,10 +478,13 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
 
   // ---- output: O = O^T / l (zero when no key is valid), LSE = m + ln l,
   // through the staging area.  Buffer stores: rows past Lq address past the
-  // records and are dropped, so every wave issues exactly kOutStores store
-  // instructions.
+  // records and are dropped.
   auto store_o = [&](uint16_t* stage, float l, bool empty) __attribute__((always_inline)) {
     const float inv = empty ? 0.f : 1.0f / l;
+    // formed here: shared with dma_q, the rows' offsets would be held (in
+    // scratch) through the whole kernel
+    int l16 = lane >> 4;
+    asm("" : "+v"(l16));
     // the lane's row l32, d = 32 mb + 8 g + 4 hi .. + 3: half hi of chunk 4 mb + g
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
@@ -511,7 +500,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
         (void*)(a.o + (size_t)b * a.Lq * tok + (size_t)h * D), (short)0, a.Lq * rbytes, kBufferFlags);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int r = 4 * i + (lane >> 4);
+      const int r = 4 * i + l16;
       const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * D + (lane & 15) * 8);
       const int grow = row0 + r;
       const int off = grow < a.Lq ? grow * rbytes + stage_slot(lane & 15, r) * 16 : 0x7ffffff0;

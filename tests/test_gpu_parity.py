@@ -265,6 +265,9 @@ RAGGED = [
     # batch, so each XCD's run holds a part of every batch (eighths of 8 and
     # 7 tiles) and the position -> tile map is exercised past its one-batch case
     inputs.custom("mixed_lengths", B=3, H=5, Lq=3000, Lk=2500, seed=27, kv_valid=("fixed", [2500, 70, 1900])),
+    # the first shape with as many heads as take it past one round of 128-row
+    # tiles, to the 256-row kernel: rotated prefix, text suffix, ragged lengths
+    inputs.custom("many_self", B=2, H=18, Lq=1000, Lk=1000, seed=21, grid=(2, 20, 24), kv_valid=("fixed", [1000, 517])),
 ]
 
 
@@ -304,7 +307,7 @@ def test_naive_kernel_agrees(w):
     _full_case(w, impl=vx.attn_fwd_naive)
 
 
-@pytest.mark.parametrize("w", [inputs.WORKLOADS["tiny"], RAGGED[0], RAGGED[5]], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [inputs.WORKLOADS["tiny"], RAGGED[0], RAGGED[5], RAGGED[7]], ids=lambda w: w.name)
 def test_prerotated_keys(w):
     """vidax_rope3d on k, then attention rotating only q: same result as the
     fused rotation of both, against the oracle."""
@@ -334,9 +337,8 @@ def test_prerotated_keys(w):
 def test_two_key_groups(mode, Lq, lens):
     """The kernel of launches with few query tiles (128 rows, alternate 32-key
     tiles to two groups, merged at the end): valid lengths at the edges of the
-    groups' tiles and of its four-buffer loop, in every rotation mode; text
-    tokens past the grid; and a launch one workgroup past its limit, which the
-    256-row kernel takes."""
+    groups' tiles and of its four-buffer loop, in every rotation mode, and text
+    tokens past the grid."""
     import dataclasses
 
     import torch
@@ -360,28 +362,30 @@ def test_two_key_groups(mode, Lq, lens):
 
 
 def test_two_key_groups_agree_with_the_dense_kernel():
-    """The same head in a launch of 128 rows x 2 heads (two key groups) and
-    among 260 heads (one workgroup of 128 rows too many: the 256-row kernel):
-    the results differ by roundings of P and of the output only."""
+    """The same heads as one workgroup of 128 rows for every compute unit (two
+    key groups) and with one head more (the 256-row kernel): the results differ
+    by roundings of P and of the output only."""
     import torch
 
+    units = torch.cuda.get_device_properties(0).multi_processor_count
     g = torch.Generator(device="cuda")
     g.manual_seed(53)
-    q, k, v = (torch.randn((1, n, 260, 128), generator=g, device="cuda").to(torch.bfloat16) for n in (100, 600, 600))
-    log("case two key groups against the dense kernel")
+    q, k, v = (torch.randn((1, n, units + 1, 128), generator=g, device="cuda").to(torch.bfloat16) for n in (100, 600, 600))
+    log(f"case two key groups against the dense kernel, {units} and {units + 1} workgroups")
     dense, ld = vx.attn_fwd(q, k, v, return_lse=True)
-    few, lf = vx.attn_fwd(*(x[:, :, :2].contiguous() for x in (q, k, v)), return_lse=True)
+    few, lf = vx.attn_fwd(*(x[:, :, :units].contiguous() for x in (q, k, v)), return_lse=True)
     torch.cuda.synchronize()
-    a, b = few.float(), dense[:, :, :2].float()
+    a, b = few.float(), dense[:, :, :units].float()
+    assert not torch.equal(a, b)  # two kernels
     assert float((a - b).norm() / b.norm()) <= 1e-2
     assert float((a - b).abs().max()) <= MAX_ABS
     # each row sum adds p rounded to bf16 (relative error at most 2^-9 each, of
     # different roundings where the reference differs): ln of it is off by at
     # most 2^-9 on either side
-    assert float((lf - ld[:, :2]).abs().max()) <= 2.0 ** -8
+    assert float((lf - ld[:, :units]).abs().max()) <= 2.0 ** -8
 
 
-@pytest.mark.parametrize("w", [inputs.WORKLOADS["tiny"], RAGGED[0], RAGGED[5]], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [inputs.WORKLOADS["tiny"], RAGGED[0], RAGGED[5], RAGGED[7]], ids=lambda w: w.name)
 def test_half_split_pairs_prerotated_keys(w):
     """Half-split pairs (channel o_a + j with o_a + j + d_a/2): k rotated by
     vidax_rope3d, q inside the attention kernel (each channel's partner from
@@ -477,9 +481,14 @@ def test_scale_values(scale):
         assert_parity(ob, ro2, f"scale {scale} exact")
 
 
-def test_peaked_and_rescaling_logits():
+@pytest.mark.parametrize("copies", [1, 17], ids=["two_key_groups", "dense"])
+@pytest.mark.parametrize("mode", ["none", "fused", "prerotated", "half"])
+def test_peaked_and_rescaling_logits(mode, copies):
     """Scores that grow along the keys force a rescale of the running sum at
-    every tile; a large scale makes the softmax nearly one-hot."""
+    every tile; a large scale makes the softmax nearly one-hot.  Two heads (few
+    query tiles), and 17 copies of them (the 256-row kernel), every copy with
+    the same bits.  With a rotation only token 0 lies on the grid, and position 0
+    turns by no angle: the rotated kernels meet the same scores."""
     import torch
 
     B, L, H, d = 1, 1000, 2, 128
@@ -493,19 +502,32 @@ def test_peaked_and_rescaling_logits():
     vf = rng.standard_normal((B, L, H, d)).astype(np.float32)
     q, k, v = (inputs.f32_to_bf16_bits(a).reshape(a.shape) for a in (qf, kf, vf))
     dec = oracle.bf16_bits_to_f64
+    rope = None if mode == "none" else vx.Rope(grid=(1, 1, 1), pair_mode=int(mode == "half"),
+                                               keys_prerotated=mode != "fused")
+    many = lambda x: to_dev(np.ascontiguousarray(np.tile(x, (1, 1, copies, 1))))
     for scale in (1.0, 30.0):
-        log(f"case peaked scale={scale}")
-        o, l = vx.attn_fwd(to_dev(q), to_dev(k), to_dev(v), scale=scale, return_lse=True)
+        log(f"case peaked {mode} x{copies} scale={scale}")
+        # the rotated kernels round the query times scale * log2(e) to bf16 before
+        # the products (as documented): the reference takes the same queries
+        qr = dec(q)
+        if rope is not None:
+            c = float(np.float32(np.float32(scale) * np.float32(1.4426950408889634)))
+            qr = dec(oracle.f64_to_bf16_bits(qr * c)) / c
+        o, l = vx.attn_fwd(many(q), many(k), many(v), scale=scale, rope=rope, return_lse=True)
         torch.cuda.synchronize()
-        ro, rl = oracle.attn_ref(dec(q), dec(k), dec(v), scale)
-        assert_parity(to_bits(o), ro, f"peaked {scale}")
-        assert_lse(l.cpu().numpy(), rl, f"peaked {scale}")
+        ro, rl = oracle.attn_ref(qr, dec(k), dec(v), scale)
+        ob, lse = to_bits(o), l.cpu().numpy()
+        assert_parity(ob[:, :, :H], ro, f"peaked {scale}")
+        assert_lse(lse[:, :H], rl, f"peaked {scale}")
+        for i in range(1, copies):
+            assert np.array_equal(ob[:, :, i * H:(i + 1) * H], ob[:, :, :H]), i
+            assert np.array_equal(lse[:, i * H:(i + 1) * H], lse[:, :H]), i
 
 
-def test_deterministic():
+@pytest.mark.parametrize("w", [RAGGED[0], RAGGED[7]], ids=lambda w: w.name)
+def test_deterministic(w):
     import torch
 
-    w = RAGGED[0]
     q, k, v, lv = inputs.make_qkv(w)
     qd, kd, vd, ld = to_dev(q), to_dev(k), to_dev(v), lengths_dev(lv)
     log("case determinism")
