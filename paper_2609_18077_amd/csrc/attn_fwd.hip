@@ -607,19 +607,6 @@ bool attn_rope_supported(const RopeParams& rp) {
   return entries <= kAttnTableMax;
 }
 
-// Compute units of the current device (queried once per device).
-static int cu_count() {
-  static int counts[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (counts[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    counts[dev] = n;
-  }
-  return counts[dev];
-}
-
 hipError_t launch_attn_fwd(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* o,
                            float* lse, int B, int H, int Lq, int Lk, float scale,
                            const int32_t* kv_valid_len, const RopeParams& rp, hipStream_t stream) {
@@ -648,7 +635,7 @@ hipError_t launch_attn_fwd(const uint16_t* q, const uint16_t* k, const uint16_t*
   }
   // short key sequences without rotation: one persistent workgroup per CU
   // (the per-workgroup scan over the batch lengths bounds B)
-  const int cus = cu_count();
+  const int cus = device_cu_count();
   if (!rp.enabled && Lk <= kAttnShortKeys && nwg > 4L * cus && B <= 4096)
     return launch_xattn_fwd(q, k, v, o, lse, B, H, Lq, Lk, scale, kv_valid_len, cus, stream);
   if (use_split(Lq, B, H, Lk, cus)) {

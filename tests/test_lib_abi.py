@@ -281,3 +281,18 @@ def test_binding_fails_loudly_without_library(monkeypatch):
     monkeypatch.setattr(vx, "LIB_PATH", "/nonexistent/libvidax.so")
     with pytest.raises(RuntimeError, match="no fallback"):
         vx.lib()
+
+
+def test_compute_units_are_asked_for_in_one_place():
+    """The count of compute units decides between kernels and is kept per
+    device: one function reads and fills the table, under its lock."""
+    import glob
+
+    srcs = {os.path.basename(p): open(p).read() for p in glob.glob(os.path.join(os.path.dirname(vx.__file__), "csrc", "*"))}
+    asking = [n for n, s in srcs.items() for _ in range(s.count("hipDeviceAttributeMultiprocessorCount"))]
+    assert len(asking) == 1, asking
+    body = srcs[asking[0]]
+    body = body[body.index("int device_cu_count() {"):]
+    body = body[:body.index("\n}")]
+    assert "hipDeviceAttributeMultiprocessorCount" in body
+    assert body.index("std::lock_guard") < body.index("counts[dev] == 0")
