@@ -235,6 +235,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
         pk.y = pack_bf16x2(acc[mb][4 * g + 2] * mul, acc[mb][4 * g + 3] * mul);
         *reinterpret_cast<uint2*>(area + l32 * D + ((4 * mb + g) ^ swz(l32)) * 8 + 4 * hi) = pk;
       }
+    wave_lds_fence();
     const __amdgpu_buffer_rsrc_t rs = rows_rsrc(a.dq);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {

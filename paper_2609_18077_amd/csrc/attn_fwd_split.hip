@@ -495,6 +495,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
         pk[1] = pack_bf16x2(oacc[mb][4 * g + 2] * inv, oacc[mb][4 * g + 3] * inv);
         *reinterpret_cast<u32x2*>(stage + l32 * D + stage_slot(4 * mb + g, l32) * 8 + 4 * hi) = pk;
       }
+    wave_lds_fence();
     // whole rows out: slot lane & 15 of row 4 i + (lane >> 4) holds chunk stage_slot(lane & 15, row)
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(a.o + (size_t)b * a.Lq * tok + (size_t)h * D), (short)0, a.Lq * rbytes, kBufferFlags);
@@ -524,7 +525,10 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
   }
   __builtin_amdgcn_s_waitcnt(0);  // this wave's query rows have landed
   {
-    if (HALF) rotate_staged_half_split();
+    if (HALF) {
+      rotate_staged_half_split();
+      wave_lds_fence();
+    }
     uint4 raw[8];
     read_q(raw);
     make_q(raw);
@@ -573,6 +577,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_split_kernel(AttnArgs a) {
         oacc[mb][4 * g + 3] = fmaf(v.w, f1, oacc[mb][4 * g + 3] * f0);
       }
     mref = mx;
+    wave_lds_fence();  // the wave's part is read before its lanes write over it
     store_o(buf, l, false);  // staged in the area that only this wave reads
   }
 }

@@ -15,7 +15,7 @@
 // its chunk before any lane of the row writes, so y may alias x.  With
 // half-split pairs a channel's partner (d_a / 2 further in its axis block)
 // sits in another lane: the row's normalised fp32 values pass through a
-// per-row LDS buffer of the 16 lanes (one wave's lanes, so no
+// per-row LDS buffer of the 16 lanes (one wave's: a fence for the compiler, no
 // barrier), and
 // each lane forms the angles of its 8 channels rather than of 4 pairs.
 #include "launch.hpp"
@@ -151,11 +151,13 @@ __global__ __launch_bounds__(kThreads) void qk_norm_kernel(QkNormArgs a) {
             // 16 lanes of this row (one wave, in order)
             *reinterpret_cast<float4*>(row + 8 * c) = make_float4(yv[0], yv[1], yv[2], yv[3]);
             *reinterpret_cast<float4*>(row + 8 * c + 4) = make_float4(yv[4], yv[5], yv[6], yv[7]);
+            wave_lds_fence();
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const float yp = row[hpart[e]];
               zv[e] = hfirst[e] ? fmaf(yv[e], hcs[e], -yp * hsn[e]) : fmaf(yp, hsn[e], yv[e] * hcs[e]);
             }
+            wave_lds_fence();
           } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) zv[e] = yv[e];

@@ -15,7 +15,7 @@
 // heads 7.2 -> 6.4 us).
 // Half-split pairs: a channel's partner lies d_a / 2 channels away, usually in
 // another lane's chunk, so the row's values pass through an LDS buffer written
-// and read by the row's 16 lanes (one wave's, in order: no
+// and read by the row's 16 lanes (one wave's: a fence for the compiler, no
 // barrier), and a lane forms the angles of its 8 channels instead of 4 pairs
 // (an LDS table per workgroup and two barriers a row before: 8200 x 24 heads
 // 27.2 -> 19.8 us, 1560 x 12 12.0 -> 6.1; interleaved pairs 18.1 -> 17.5 and
@@ -113,6 +113,7 @@ __global__ __launch_bounds__(kThreads) void rope3d_kernel(Rope3dArgs a) {
       if (HALF) {
         uint16_t* const row = rows + (4 * (threadIdx.x >> 4) + u) * kHeadDim;
         *reinterpret_cast<u32x4*>(row + 8 * c) = v[u];
+        wave_lds_fence();
         float y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(kThreads) void rope3d_kernel(Rope3dArgs a) {
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) o[p] = pack_bf16x2(y[2 * p], y[2 * p + 1]);
+        wave_lds_fence();
       } else {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
