@@ -316,9 +316,9 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a) {
   // work.  S of block 0, dP of block 0 beside its exponentials, S of block 1
   // beside dS of block 0, dP of block 1 beside its exponentials, dQ of block 0
   // beside dS of block 1, dQ of block 1: no product waits for the vector work
-  // before it.  At 32760 x 32760 x 12 heads: matrix cores busy 64 -> 76 % of the
-  // cycles, 8.16 -> 7.60 ms (the clock falls from 1.82 to 1.63 GHz: at this load
-  // the board's power holds it).  TAIL: the last tile, whose keys past Lv get P = 0.
+  // before it.  At 32760 x 32760 x 12 heads: 8.16 -> 7.60 ms, matrix cores busy 80 %
+  // of the cycles, at the clock (1.6 GHz of 2.4) that the board's power limit
+  // leaves.  TAIL: the last tile, whose keys past Lv get P = 0.
   auto step = [&](auto par, auto tl, int j) __attribute__((always_inline)) {
     constexpr int P = decltype(par)::value;
     constexpr bool TAIL = decltype(tl)::value;
@@ -422,11 +422,8 @@ __global__ __launch_bounds__(512) void bwd_dq8_kernel(BwdArgs a) { dq_body<8>(a)
 // A workgroup with at most 128 valid keys gives each of its 32-key groups to
 // two waves, which take alternate query blocks and add up at the end (short
 // texts would leave more than half of the waves idle).  So does every workgroup
-// of a launch whose 128-key tiles still fit the compute units in one round
-// (unsplit): half the chain per workgroup and no partials.  Whole
-// call with forward and rotations, against runs of 2 query tiles: 2 heads x 512
-// tokens 84.2 -> 79.6 us, 12 x 510 82.0 -> 79.5; forward and backward of 80 x
-// 500 queries x 300 keys 68.4 -> 57.8.
+// of a launch with 128 keys a workgroup (kper; the rule is at attn_bwd_split):
+// half the chain per workgroup where that takes no more rounds.
 constexpr int BK = kBwdKeys;  // keys per workgroup
 constexpr int KOWN = 32 * D;  // elements of one wave's own keys in LDS
 
@@ -591,9 +588,8 @@ __global__ __launch_bounds__(NT) void bwd_dkdv_kernel(BwdArgs a) {
         // operand reads of the product three slots later and its share of
         // the vector work, so that a wave waits neither for LDS nor for its
         // exponentials (left to the compiler, every score product waited for
-        // a read issued just before it).  At 32760 x 32760 x 12 heads: matrix
-        // cores busy 58 -> 73 % of the cycles, 11.2 -> 10.3 ms (clock 1.94 ->
-        // 1.68 GHz).
+        // a read issued just before it).  At 32760 x 32760 x 12 heads: 11.2 ->
+        // 10.3 ms, matrix cores busy 77 % of the cycles.
         const uint16_t* qb = qt + 32 * blk * D;
         const uint16_t* ob = ot + 32 * blk * D;
         f32x16 s = f32x16{}, dp;
