@@ -184,7 +184,7 @@ vidax_status vidax_attn_fwd(const void* q, const void* k, const void* v, void* o
  *           handled by separate workgroups, their partial dK and dV summed
  *           in fp32 in the rest of the workspace (faster when
  *           B * H * ceil(Lk / 256) is small against the compute units, e.g.
- *           text cross-attention; at most 192 MiB); with fewer values they
+ *           text cross-attention; at most 384 MiB); with fewer values they
  *           take the runs that fit, or run unsplit.  All give the same
  *           gradients up to the order of the fp32 sums.
  *   scale, kv_valid_len: as for vidax_attn_fwd.

@@ -88,13 +88,15 @@ int device_cu_count();
 // Runs are considered where full workgroups number less than twice the compute
 // units and there are more than 8 query tiles (up to 8, unsplit was faster by
 // 3 to 22 %), as far as the partials stay within kBwdPartFloats and the whole
-// within max_floats.  192 MiB is what the runs of a launch that fills the chip
-// come to; without that line 3 heads x 39167 took five runs and 601 MB for 6569
-// us, against 6508 us unsplit.  The partials follow D in the workspace, from a
+// within max_floats.  The line is 384 MiB because larger partials won nothing:
+// 3 heads x 39167 took five runs and 601 MB for 6569 us, against 6508 unsplit;
+// 2 x 2 heads x 28000 four runs and 459 MB for 4431, against 4381.  Half of it
+// was slower: 3 heads x 23058, two runs and 142 MB 3037 us, five runs and 354
+// MB 2901.  The partials follow D in the workspace, from a
 // 256-byte aligned offset; `floats` is the workspace the choice needs (B * H * Lq
 // when qsplit is 1).
 constexpr int kBwdKeys = 256;
-constexpr size_t kBwdPartFloats = (size_t)48 << 20;
+constexpr size_t kBwdPartFloats = (size_t)96 << 20;
 struct BwdSplit {
   int kper, qsplit, qper;
   size_t part_offset, floats;

@@ -108,7 +108,7 @@ def _bwd_shapes():
 
 def test_bwd_split_fits_its_workspace(rules):
     """Every query tile lies in one run, the partials end within the workspace
-    the rule asks for and within 192 MiB, and a call with any smaller workspace
+    the rule asks for and within 384 MiB, and a call with any smaller workspace
     (down to D alone) takes runs that fit it."""
     for B, H, Lq, Lk in _bwd_shapes():
         tiles, rows, run = -(-Lq // 64), B * H * Lq, 2 * B * H * Lk * 128
@@ -123,7 +123,7 @@ def test_bwd_split_fits_its_workspace(rules):
                 assert kper in (128, 256) and (qsplit == 1 or kper == 256)
                 if qsplit > 1:
                     assert off % 64 == 0 and off >= rows and floats == off + qsplit * run
-                    assert qsplit * run * 4 <= 192 << 20
+                    assert qsplit * run * 4 <= 384 << 20
                 else:
                     assert floats == rows
 
@@ -136,6 +136,14 @@ def test_bwd_split_with_a_smaller_workspace_keeps_splitting(rules):
     assert _bwd(rules, B, H, Lq, Lk)[1] == 20
     for s in (2, 8, 16, 19):
         assert s // 2 < _bwd(rules, B, H, Lq, Lk, rows + 64 + s * run)[1] <= s, s
+
+
+def test_bwd_split_bound_keeps_the_runs_that_pay(rules):
+    """Runs on both sides of the bound on the partials."""
+    assert _bwd(rules, 1, 3, 23058, 23058)[1] == 5  # 354 MB: 2901 us, two runs 3037
+    assert _bwd(rules, 2, 3, 11520, 11520)[1] == 4  # 283 MB: 1527 us, two runs 1557
+    assert _bwd(rules, 1, 3, 39167, 39167)[1] == 1  # five runs, 601 MB: 6569 us, unsplit 6508
+    assert _bwd(rules, 2, 2, 28000, 28000)[1] == 1  # four runs, 459 MB: 4431 us, unsplit 4381
 
 
 def test_bwd_key_workgroups(rules):
